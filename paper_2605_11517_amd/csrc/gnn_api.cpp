@@ -409,6 +409,7 @@ namespace gnnmi {
 SpmmItems plan_items(const HostMeta::Plan& H, const DevMeta::Plan& P, int32_t p)
 {
     SpmmItems it;
+    it.segment = H.segment;
     const int64_t r0 = H.range_off[(size_t)p], s0 = H.seg_off[(size_t)p], l0 = H.long_off[(size_t)p];
     it.nranges = H.range_off[(size_t)p + 1] - r0 - 1;
     if (it.nranges < 0) it.nranges = 0;

@@ -11,6 +11,12 @@
 
 namespace gnnmi {
 
+// Rows with more entries than HostMeta::segment are cut into segments of that many entries, each
+// handled by its own slot or wavefront; shorter rows are grouped into ranges of about that many
+// entries.  At most kSpmmSegmentMax (the attention passes keep a short row's scores in registers).
+constexpr int32_t kSpmmSegmentMax = 512;
+constexpr int32_t kSpmmRangeRows = 64;
+
 // Host-side partition metadata.  "row" always means a vertex in library order
 // (partition-major, ascending original id inside a partition).
 struct HostMeta {
@@ -54,7 +60,9 @@ struct HostMeta {
     int32_t part_iterations = 0;          // switching-aware partitioner: iterations run
     std::vector<double> part_objective;   // and the mean score per vertex of every state
     // work decomposition of the aggregation kernels (forward operator and its transpose)
+    int32_t segment = kSpmmSegmentMax;    // entries per segment of a long row
     struct Plan {
+        int32_t segment = kSpmmSegmentMax;
         std::vector<int64_t> range_off;   // k+1, offsets into range_rows (partition p has
                                           // range_off[p+1]-range_off[p] boundaries = ranges + 1)
         std::vector<int32_t> range_rows;  // local row boundaries of consecutive row ranges
@@ -82,11 +90,6 @@ struct HostMeta {
         bool ready = false;
     } masked_t;
 };
-
-// Rows with more entries than this are cut into segments of this many entries, each handled
-// by its own wavefront; shorter rows are grouped into ranges of about this many entries.
-constexpr int32_t kSpmmSegment = 512;
-constexpr int32_t kSpmmRangeRows = 64;
 
 // Builds everything above.  Returns GNN_OK or an error with `err` set.
 gnn_status build_host_meta(int model, int64_t n, const int64_t* rowptr, const int32_t* colidx,
@@ -129,6 +132,7 @@ struct SpmmItems {
     const int32_t* rows_sorted = nullptr;  // short rows, longest first (column-sliced kernel)
     int64_t nshort = 0;
     float avg_len = 0.f;                   // entries per row of this operator block (0: not known)
+    int32_t segment = kSpmmSegmentMax;     // rows with more entries are listed as segments
 };
 // Optional fused scatter-accumulate for fp32 outputs: instead of out[r,:] = value, the kernel
 // does out[map(r),:] += value with map(r) = base_row + r for r < n_own and idx[r - n_own]

@@ -62,6 +62,7 @@ struct GatRows {
     int64_t nranges;
     const int32_t* long_row;
     int64_t nlong;
+    int32_t segment;            // longer rows are handled segment by segment
     __device__ float ssrc(int32_t c, int32_t h) const
     {
         return c < n_own ? ssrc_own[(int64_t)c * nh + h] : ssrc_bnd[(int64_t)(c - n_own) * nh + h];
@@ -102,10 +103,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_scores(const float* __restrict__
     }
 }
 
-// attention weights of one short row (at most kSpmmSegment = 8 x 64 entries):
+// attention weights of one short row (at most kSpmmSegmentMax = 8 x 64 entries):
 // att[e - e0] = softmax over the row's entries of LeakyReLU(s_src(col) + s_dst(row)).  Every
 // lane keeps its up to eight scores in registers, so the scores are gathered once.
-constexpr int kPerLane = kSpmmSegment / kWave;
+constexpr int kPerLane = kSpmmSegmentMax / kWave;
 
 // The row-wise passes take HB heads of a row at a time (h0 .. h0 + HB - 1, those below nh):
 // the scores of the HB heads of a neighbour lie side by side and are fetched together (VEC: as
@@ -318,7 +319,7 @@ __device__ inline void att_rows_groups(const GatRows& g, int32_t r0, int32_t r1,
         if (row < r1) {
             eb = g.rp[row];
             ee = g.rp[row + 1];
-            if (ee - eb > kGroupRow) ee = eb;           // longer rows: a whole wavefront each, afterwards
+            if (ee - eb > (g.segment < kGroupRow ? g.segment : kGroupRow)) ee = eb;   // longer rows: afterwards
         }
         const int niter = (int)((ee - eb + kGroup - 1) / kGroup);
         int32_t cols[kPerLane];
@@ -395,7 +396,7 @@ __device__ inline void bwd_rows_groups(const GatRows& g, int32_t r0, int32_t r1,
         if (row < r1) {
             eb = g.rp[row];
             ee = g.rp[row + 1];
-            if (ee - eb > kGroupRow) ee = eb;           // longer rows: a whole wavefront each, afterwards
+            if (ee - eb > (g.segment < kGroupRow ? g.segment : kGroupRow)) ee = eb;   // longer rows: afterwards
         }
         const int niter = (int)((ee - eb + kGroup - 1) / kGroup);
         int32_t cols[kPerLane];
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_rows(const GatRows g, float* __r
     else bwd_rows_groups<HB, VEC>(g, g.range_rows[item], r1, att, dal, pair, gs_dst_own);
     for (int32_t row = g.range_rows[item]; row < r1; ++row) {
         const int64_t len = g.rp[row + 1] - g.rp[row];
-        if (len > kSpmmSegment || len <= kGroupRow) continue;
+        if (len > g.segment || len <= kGroupRow) continue;
         for (int32_t h0 = 0; h0 < g.nh; h0 += HB) {
             if constexpr (MODE == 0) att_row_wave<HB, VEC>(g, row, h0, att);
             else bwd_row_wave<HB, VEC>(g, row, h0, att, dal, pair, gs_dst_own);
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_rows(const GatRows g, float* __r
 }
 
 // ---- long rows, segment-parallel --------------------------------------------------------------
-// A long row is cut into segments of at most kSpmmSegment entries (the aggregation kernel's work
+// A long row is cut into segments of at most kSpmmSegmentMax entries (the aggregation kernel's work
 // items); one wavefront handles one segment with its entries in registers, a second small
 // kernel combines the segments of each row in segment order, a third applies the result.
 struct GatSegs {
@@ -694,6 +695,7 @@ struct GatTRows {
     int64_t hs;                 // tw_att one array per head, hs floats apart
     const int32_t* range_rows;
     int64_t nranges;
+    int32_t segment;
 };
 // Long transposed rows (a hub as a source: up to 10^5 destinations in one partition) are cut
 // into the aggregation's segments like the long forward rows: one wavefront per segment and all
@@ -766,7 +768,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_trows(const GatTRows g, const fl
             if (i < r1) {
                 eb = g.trp[i];
                 ee = g.trp[i + 1];
-                if (ee - eb > kSpmmSegment) ee = eb;      // long rows: the other kernel
+                if (ee - eb > g.segment) ee = eb;      // long rows: the other kernel
             }
             for (int32_t h0 = 0; h0 < g.nh; h0 += HB) {
                 const int nhb = g.nh - h0 < HB ? g.nh - h0 : HB;
@@ -913,7 +915,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dots(GatDotArgs g)
     const int32_t r1 = g.it.range_rows[ri + 1];
     for (int32_t row = g.it.range_rows[ri]; row < r1; ++row) {
         const int64_t eb = g.rp[row], ee = g.rp[row + 1];
-        if (ee - eb > kSpmmSegment) continue;
+        if (ee - eb > g.it.segment) continue;
         dot_entries<G, NV>(g, row, eb, ee, lane);
     }
 }
@@ -1014,6 +1016,7 @@ static GatRows make_rows(const GatRowsHost& h)
     g.nh = h.nh; g.hs = h.hs;
     g.range_rows = h.items.range_rows; g.nranges = h.items.nranges;
     g.long_row = h.items.long_row; g.nlong = h.items.nlong;
+    g.segment = h.items.segment;
     return g;
 }
 
@@ -1094,6 +1097,7 @@ void launch_gat_transposed(const int64_t* trp, const int32_t* tperm, int64_t e0,
     g.trp = trp; g.tperm = tperm; g.e0 = e0; g.n_own = n_own; g.base_row = base_row; g.bnd = bnd;
     g.nh = nh; g.hs = hs;
     g.range_rows = items.range_rows; g.nranges = items.nranges;
+    g.segment = items.segment;
     if (g.nranges > 0) {
         const dim3 grid((unsigned)((g.nranges + 3) / 4)), b(kBlock);
         if (nh % 2 == 0) hipLaunchKernelGGL((k_gat_trows<true>), grid, b, 0, s, g, pair, tw_att, gs_src);

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_items(const SpmmArgs g)
     const int32_t r_end = g.it.range_rows[ri + 1];
     for (int32_t row = g.it.range_rows[ri]; row < r_end; ++row) {
         const int64_t e_begin = g.rp[row], e_end = g.rp[row + 1];
-        if (e_end - e_begin > kSpmmSegment) continue;  // long row: handled by its segments
+        if (e_end - e_begin > g.it.segment) continue;  // long row: handled by its segments
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll

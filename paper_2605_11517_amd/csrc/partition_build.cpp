@@ -433,35 +433,55 @@ void assign_switching(int64_t n, const int64_t* rowptr, const int32_t* colidx, i
     }
 }
 
+// Entries per segment of a long row, by the entries of a partition (= of one aggregation launch of
+// the per-partition schedule).  A slot of G lanes walks a segment (or a short row of up to as many
+// entries) in dependent steps of four to eight source rows, about 0.15 us per entry, so the segment
+// length is the shortest time a launch can take: 70-100 us at 512 entries whatever the graph.  Short
+// segments cost partial sums (one row written and read per segment) and a longer combine chain, and
+// in a launch that fills the chip many times over nothing waits for a single slot.  Measured, whole
+// epochs in ms at 512 / 256 / 128 / 64 entries:
+//   GCN 64-64-16, 50 k entries per partition                1.31 / 1.03 / 0.79 / 0.66
+//   attention 100-256-256-47, 8 heads, 380 k                44.7 / 35.2 / 29.8 / 27.5
+//   GraphSAGE 100-256-256-47, 510 k (paper's order)         23.8 / 19.0 / 17.3 / 17.6
+//   GCN 128-128-128-172, directed, 810 k                    60.4 / 50.9 / 48.5 / 50.5
+//   GraphSAGE 100-256-256-47, 4.1 M                         41.8 / 41.5 / 42.2 / 43.8
+static int32_t segment_for(int64_t entries)
+{
+    if (entries < 450000) return 64;
+    if (entries < 1500000) return 128;
+    if (entries < 6000000) return 256;
+    return kSpmmSegmentMax;
+}
+
 // Cuts the rows [0, nrows) of one partition (row pointers rp[0..nrows], absolute positions)
-// into work items: rows longer than kSpmmSegment become segments of that many entries; the
-// others are grouped into consecutive ranges holding at most kSpmmSegment entries and
+// into work items: rows longer than `segment` become segments of that many entries; the
+// others are grouped into consecutive ranges holding at most `segment` entries and
 // kSpmmRangeRows rows (a long row closes the range before it and is skipped by range items).
 struct PlanPart {
     std::vector<int32_t> range_rows, seg_row, seg_len, long_row, long_first, long_nseg, rows_sorted;
     std::vector<int64_t> seg_begin;
 };
-void plan_partition(const int64_t* rp, int64_t nrows, PlanPart& P)
+void plan_partition(const int64_t* rp, int64_t nrows, int32_t segment, PlanPart& P)
 {
     P.range_rows.push_back(0);
     int64_t acc = 0;
     int32_t start = 0;
     for (int64_t r = 0; r < nrows; ++r) {
         const int64_t deg = rp[r + 1] - rp[r];
-        if (deg > kSpmmSegment) {
+        if (deg > segment) {
             P.long_row.push_back((int32_t)r);
             P.long_first.push_back((int32_t)P.seg_row.size());
             int32_t ns = 0;
-            for (int64_t e = rp[r]; e < rp[r + 1]; e += kSpmmSegment) {
+            for (int64_t e = rp[r]; e < rp[r + 1]; e += segment) {
                 P.seg_row.push_back((int32_t)r);
                 P.seg_begin.push_back(e);
-                P.seg_len.push_back((int32_t)std::min<int64_t>(kSpmmSegment, rp[r + 1] - e));
+                P.seg_len.push_back((int32_t)std::min<int64_t>(segment, rp[r + 1] - e));
                 ++ns;
             }
             P.long_nseg.push_back(ns);
             continue;  // costs a range nothing
         }
-        if (r > start && (acc + deg > kSpmmSegment || r - start >= kSpmmRangeRows)) {
+        if (r > start && (acc + deg > segment || r - start >= kSpmmRangeRows)) {
             P.range_rows.push_back((int32_t)r);
             start = (int32_t)r;
             acc = 0;
@@ -470,21 +490,22 @@ void plan_partition(const int64_t* rp, int64_t nrows, PlanPart& P)
     }
     if (nrows > start) P.range_rows.push_back((int32_t)nrows);
     // short rows by entry count, longest first, ascending row id among equals (counting sort)
-    std::vector<int64_t> bucket((size_t)kSpmmSegment + 2, 0);
+    std::vector<int64_t> bucket((size_t)segment + 2, 0);
     for (int64_t r = 0; r < nrows; ++r) {
         const int64_t deg = rp[r + 1] - rp[r];
-        if (deg <= kSpmmSegment) bucket[(size_t)(kSpmmSegment - deg) + 1]++;
+        if (deg <= segment) bucket[(size_t)(segment - deg) + 1]++;
     }
     for (size_t i = 1; i < bucket.size(); ++i) bucket[i] += bucket[i - 1];
     P.rows_sorted.resize((size_t)bucket.back());
     for (int64_t r = 0; r < nrows; ++r) {
         const int64_t deg = rp[r + 1] - rp[r];
-        if (deg <= kSpmmSegment) P.rows_sorted[(size_t)bucket[(size_t)(kSpmmSegment - deg)]++] = (int32_t)r;
+        if (deg <= segment) P.rows_sorted[(size_t)bucket[(size_t)(segment - deg)]++] = (int32_t)r;
     }
 }
 
-void append_plan(HostMeta::Plan& G, int32_t k, std::vector<PlanPart>& parts)
+void append_plan(HostMeta::Plan& G, int32_t k, int32_t segment, std::vector<PlanPart>& parts)
 {
+    G.segment = segment;
     G.range_off.assign((size_t)k + 1, 0);
     G.seg_off.assign((size_t)k + 1, 0);
     G.long_off.assign((size_t)k + 1, 0);
@@ -564,9 +585,9 @@ void build_masked_transpose(HostMeta& M, const uint8_t* mask)
     std::vector<PlanPart> plan((size_t)k);
     parallel_for(k, 1, [&](int, int64_t p) {
         const int64_t t0 = T.toff[(size_t)p];
-        plan_partition(T.trp.data() + t0, T.toff[(size_t)p + 1] - t0, plan[(size_t)p]);
+        plan_partition(T.trp.data() + t0, T.toff[(size_t)p + 1] - t0, M.segment, plan[(size_t)p]);
     });
-    append_plan(T.plan, k, plan);
+    append_plan(T.plan, k, M.segment, plan);
     T.ready = true;
 }
 
@@ -859,15 +880,16 @@ gnn_status build_host_meta(int model, int64_t n, const int64_t* rowptr, const in
 
         // ---- phase D: work items of the aggregation kernels -------------------------------------
         {
+            M.segment = segment_for(nnz / k);
             std::vector<PlanPart> fw((size_t)k), bw((size_t)k);
             parallel_for(k, 1, [&](int, int64_t p) {
                 const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
-                plan_partition(M.rp.data() + r0, np, fw[(size_t)p]);
+                plan_partition(M.rp.data() + r0, np, M.segment, fw[(size_t)p]);
                 const int64_t t0 = M.toff[(size_t)p], nR = M.toff[(size_t)p + 1] - t0;
-                plan_partition(M.trp.data() + t0, nR, bw[(size_t)p]);
+                plan_partition(M.trp.data() + t0, nR, M.segment, bw[(size_t)p]);
             });
-            append_plan(M.plan_fwd, k, fw);
-            append_plan(M.plan_bwd, k, bw);
+            append_plan(M.plan_fwd, k, M.segment, fw);
+            append_plan(M.plan_bwd, k, M.segment, bw);
         }
 
         // ---- stats ---------------------------------------------------------------------------
