@@ -351,7 +351,7 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
         }
         {
             Timed t(c, s, GNN_K_GEMM_DW);
-            launch_gemm_tn(in_own, v0.din, gHp, v0.ldh, gW, v0.dout, v0.din, v0.dout, v0.np, splitk, s);
+            weight_grad(c, in_own, v0.din, gHp, v0.ldh, gW, v0.dout, v0.din, v0.dout, v0.np, splitk, s);
         }
         if (gprev) {
             Timed t(c, s, GNN_K_GEMM_DZ);   // the only term of grad A^{l-1}_p: written, not accumulated
@@ -370,7 +370,7 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
             launch_colsum_finish(part + v.f, (v.np + 255) / 256, v.f, ga + v.dout + (int64_t)h * v.f, s, 2 * v.f);
         }
         Timed t(c, s, GNN_K_GEMM_DW);
-        launch_gemm_tn(in_own, v.din, gHp, v.ldh, gW + (int64_t)h * v.f, v.dout, v.din, v.f, v.np, splitk, s);
+        weight_grad(c, in_own, v.din, gHp, v.ldh, gW + (int64_t)h * v.f, v.dout, v.din, v.f, v.np, splitk, s);
     }
     if (gprev) {
         // grad A^{l-1}_p = sum over heads of grad H_p W^T on the head's columns: written by the

@@ -253,26 +253,89 @@ void update_stream_xf(gnn_ctx* c)
     c->stream_xf_ok = c->xf_buffer_bytes(c->M.n) + 2 * array + 4 * blk <= c->hbm_budget / 256 * 256;
 }
 
+gnn_status check_lp(gnn_ctx* c, int32_t layer, int32_t p)
+{
+    if (!c->bound) return c->fail(GNN_ESTATE, "buffers are not bound (call gnn_bind)");
+    if (layer < 1 || layer > c->L) return c->fail(GNN_EINVAL, "layer outside 1..L");
+    if (p < 0 || p >= c->M.k) return c->fail(GNN_EINVAL, "partition outside 0..k-1");
+    if (c->streaming())
+        return c->fail(GNN_EUNSUPPORTED,
+                       "with a streaming budget only gnn_epoch drives the schedule; the per-partition "
+                       "entry points need resident buffers");
+    return GNN_OK;
+}
+
+
+// entries per row of partition p's operator
+float entries_per_row(const HostMeta& M, int32_t p)
+{
+    const int64_t r0 = M.off[(size_t)p], r1 = M.off[(size_t)p + 1];
+    const int64_t entries = M.rp.empty() ? M.stats.nnz : M.rp[(size_t)r1] - M.rp[(size_t)r0];   // (whole graph: no row pointers here)
+    return (float)entries / (float)std::max<int64_t>(1, r1 - r0);
+}
+
+// Z_p = S_p [in_own ; staging]
+void run_spmm_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, hipStream_t s)
+{
+    const HostMeta& M = c->M;
+    const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
+    const int32_t din = c->dims[(size_t)layer - 1];
+    SpmmItems items = plan_items(M.plan_fwd, c->D.fwd, p);
+    items.avg_len = entries_per_row(M, p);
+    const float* rscale = c->D.rscale ? c->D.rscale + r0 : nullptr;
+    void* Z = c->z_region(layer, p);
+    float* segpart = (float*)(c->scratch + c->ws.segpart);
+    const int b16 = c->bf16() ? 1 : 0;
+    {
+        Timed t(c, s, GNN_K_SPMM);
+        if (c->gather_fused())
+            launch_spmm(c->D.rp + r0, c->D.gcol, c->D.ew, rscale, c->layer_input(layer), M.n, nullptr, Z, np, din,
+                        b16, b16, items, segpart, 1, SpmmScatter{}, s);
+        else
+            launch_spmm(c->D.rp + r0, c->D.lcol, c->D.ew, rscale, in_own, np, c->staging, Z, np, din, b16,
+                        b16, items, segpart, 1, SpmmScatter{}, s);
+    }
+    if (items.nlong > 0) {
+        Timed t(c, s, GNN_K_SPMM_REDUCE);
+        launch_spmm_reduce(rscale, Z, din, b16, items, segpart, SpmmScatter{}, s);
+    }
+}
+
+}  // namespace
+
+namespace gnnmi {
+
+int64_t weight_grad_partial_floats(const gnn_ctx* c, int32_t m, int32_t n)
+{
+    const HostMeta& M = c->M;
+    const int64_t mn = (int64_t)m * n, rows = c->grad_rows(), chunk = gemm_tn_chunk(rows, m, n);
+    if (c->is_whole) {
+        // splits of all partitions (a last part of each) and one sum per partition and kernel
+        int64_t splits = M.n / chunk + c->parts_k;
+        if (c->bf16()) splits += M.n / gemm_bf16_tn_wide_chunk(rows, m, n) + c->parts_k;
+        return (splits + 2 * (int64_t)c->parts_k) * mn;
+    }
+    int64_t splits = M.stats.max_own / chunk + 1;
+    if (c->bf16()) splits = std::max(splits, M.stats.max_own / gemm_bf16_tn_wide_chunk(rows, m, n) + 1);
+    return splits * mn;
+}
+
 void compute_workspace(gnn_ctx* c)
 {
     update_stream_xf(c);
     const HostMeta& M = c->M;
     const int32_t L = c->L;
     int64_t max_np = M.stats.max_own, max_b = M.stats.max_boundary, max_r = 0;
-    for (int32_t p = 0; p < M.k; ++p)
+    // (the whole-graph schedule leaves no gathered-row gradient in scratch and has no side stream)
+    for (int32_t p = 0; p < M.k && !c->is_whole; ++p)
         max_r = std::max(max_r, M.toff[(size_t)p + 1] - M.toff[(size_t)p]);
     int64_t din = 0, dout = 0, part = 0;
     for (int32_t l = 0; l < L; ++l) {
         din = std::max<int64_t>(din, c->dims[(size_t)l]);
         dout = std::max<int64_t>(dout, c->dims[(size_t)l + 1]);
-        int sp = gemm_tn_splits(max_np, c->dims[(size_t)l], c->dims[(size_t)l + 1]);
-        part = std::max(part, (int64_t)sp * c->dims[(size_t)l] * c->dims[(size_t)l + 1]);
-        if (c->nheads(l + 1) > 1) {   // the weight gradient is taken head by head
-            sp = gemm_tn_splits(max_np, c->dims[(size_t)l], c->head_cols(l + 1));
-            part = std::max(part, (int64_t)sp * c->dims[(size_t)l] * c->head_cols(l + 1));
-        }
-        if (c->bf16())
-            part = std::max(part, gemm_bf16_tn_partial_floats(max_np, c->dims[(size_t)l], c->dims[(size_t)l + 1]));
+        part = std::max(part, weight_grad_partial_floats(c, c->dims[(size_t)l], c->dims[(size_t)l + 1]));
+        if (c->nheads(l + 1) > 1)     // the weight gradient is taken head by head
+            part = std::max(part, weight_grad_partial_floats(c, c->dims[(size_t)l], c->head_cols(l + 1)));
     }
     // rows that pass through staging, Z, the padded dY copy and the segment partial sums are as
     // wide as the widest aggregated row: an input width, or the padded output width of a layer
@@ -283,22 +346,24 @@ void compute_workspace(gnn_ctx* c)
     w.staging_bytes = align_up(std::max<int64_t>(1, max_b * din * 4));
     int64_t o = 0;
     auto take = [&](int64_t floats) { int64_t at = o; o += align_up(std::max<int64_t>(1, floats) * 4); return at; };
-    w.z = take(max_np * din);
-    w.z2 = take(max_np * din);
+    // (the loss and the kept aggregates first: they lie at the same place in both schedules' layouts)
+    w.scalars = take(64);
     w.zkeep.assign((size_t)L, -1);
     if (c->keep_forward && c->model != GNN_GAT && !c->streaming())
         for (int32_t l = 1; l <= L; ++l)
             if (!c->transform_first(l))      // n rows of the layer's input width, storage type
                 w.zkeep[(size_t)l - 1] = take((M.n * (int64_t)c->dims[(size_t)l - 1] * c->es() + 3) / 4);
+    w.z = take(max_np * din);
+    w.z2 = c->is_whole ? w.z : take(max_np * din);
     w.dy = take(max_np * dout);
     w.dz = take(max_np * din);
     w.dga = take(max_r * din);
     w.partial = take(part);
-    w.partial2 = take(part);
+    w.partial2 = c->is_whole ? w.partial : take(part);
+    // (whole graph: a part of a block and a sum of its own for every partition)
     w.colpart = take(std::max(act_bwd_partial_floats(max_np, (int32_t)dout),
-                              gat_rank1_partial_floats(max_np, (int32_t)dout)));
-    w.losspart = take(loss_partial_floats(M.n, M.k));
-    w.scalars = take(64);
+                              gat_rank1_partial_floats(max_np, (int32_t)dout)) + 2 * (int64_t)c->parts_k * dout);
+    w.losspart = take(loss_partial_floats(M.n, std::max(M.k, c->parts_k)));
     w.segpart = take(std::max(M.plan_fwd.max_segs, M.plan_bwd.max_segs) * din);
     if (c->bf16()) {
         int64_t wmax = 0;
@@ -360,51 +425,8 @@ void compute_workspace(gnn_ctx* c)
         w.pair = take(M.stats.max_nnz * mh * 2);
     }
     w.scratch_bytes = o;
+    if (!c->is_whole) whole_layout(c);
 }
-
-gnn_status check_lp(gnn_ctx* c, int32_t layer, int32_t p)
-{
-    if (!c->bound) return c->fail(GNN_ESTATE, "buffers are not bound (call gnn_bind)");
-    if (layer < 1 || layer > c->L) return c->fail(GNN_EINVAL, "layer outside 1..L");
-    if (p < 0 || p >= c->M.k) return c->fail(GNN_EINVAL, "partition outside 0..k-1");
-    if (c->streaming())
-        return c->fail(GNN_EUNSUPPORTED,
-                       "with a streaming budget only gnn_epoch drives the schedule; the per-partition "
-                       "entry points need resident buffers");
-    return GNN_OK;
-}
-
-
-// Z_p = S_p [in_own ; staging]
-void run_spmm_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, hipStream_t s)
-{
-    const HostMeta& M = c->M;
-    const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
-    const int32_t din = c->dims[(size_t)layer - 1];
-    SpmmItems items = plan_items(M.plan_fwd, c->D.fwd, p);
-    items.avg_len = (float)(M.rp[(size_t)M.off[(size_t)p + 1]] - M.rp[(size_t)r0]) / (float)std::max<int64_t>(1, np);
-    const float* rscale = c->D.rscale ? c->D.rscale + r0 : nullptr;
-    void* Z = c->z_region(layer, p);
-    float* segpart = (float*)(c->scratch + c->ws.segpart);
-    const int b16 = c->bf16() ? 1 : 0;
-    {
-        Timed t(c, s, GNN_K_SPMM);
-        if (c->gather_fused())
-            launch_spmm(c->D.rp + r0, c->D.gcol, c->D.ew, rscale, c->layer_input(layer), M.n, nullptr, Z, np, din,
-                        b16, b16, items, segpart, 1, SpmmScatter{}, s);
-        else
-            launch_spmm(c->D.rp + r0, c->D.lcol, c->D.ew, rscale, in_own, np, c->staging, Z, np, din, b16,
-                        b16, items, segpart, 1, SpmmScatter{}, s);
-    }
-    if (items.nlong > 0) {
-        Timed t(c, s, GNN_K_SPMM_REDUCE);
-        launch_spmm_reduce(rscale, Z, din, b16, items, segpart, SpmmScatter{}, s);
-    }
-}
-
-}  // namespace
-
-namespace gnnmi {
 
 SpmmItems plan_items(const HostMeta::Plan& H, const DevMeta::Plan& P, int32_t p)
 {
@@ -471,6 +493,26 @@ void apply_dropout(gnn_ctx* c, int32_t layer, int64_t r0, int64_t rows, void* ou
     const uint32_t threshold = (uint32_t)std::floor((double)c->dropout_p * 4294967296.0);
     launch_dropout(out_own, is_bf16, c->D.order + r0, rows, c->dims[(size_t)layer], key, threshold,
                    1.f / (1.f - c->dropout_p), s);
+}
+
+static const RowBlocks* row_blocks(const gnn_ctx* c) { return c->is_whole ? &c->tables.rb : nullptr; }
+
+void weight_grad(gnn_ctx* c, const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t ldc, int32_t m,
+                 int32_t n, int64_t rows, float* partial, hipStream_t s)
+{
+    const int64_t grad_rows = c->grad_rows(), chunk = gemm_tn_chunk(grad_rows, m, n);
+    const WholeTables::Split* sp = nullptr;
+    if (c->is_whole) {
+        const int64_t wide = c->bf16() && gemm_bf16_tn_wide_ok(grad_rows, m, n, lda, ldb)
+                                 ? gemm_bf16_tn_wide_chunk(grad_rows, m, n) : 0;
+        sp = &c->tables.splits.at({wide, chunk});          // built by whole_bind for every layer's product
+    }
+    if (c->bf16())
+        launch_gemm_bf16_tn(a, lda, b, ldb, out, ldc, m, n, rows, grad_rows, partial, s, sp ? &sp->wide : nullptr,
+                            sp ? &sp->narrow : nullptr);
+    else
+        launch_gemm_tn((const float*)a, lda, (const float*)b, ldb, out, ldc, m, n, rows, chunk, partial, s,
+                       sp ? &sp->narrow : nullptr);
 }
 
 void compute_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, char* out_own, hipStream_t s)
@@ -625,7 +667,6 @@ const char* compute_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own
     const HostMeta& M = c->M;
     const int32_t L = c->L;
     const int64_t np = M.off[(size_t)p + 1] - M.off[(size_t)p];
-    const int64_t nb = M.boff[(size_t)p + 1] - M.boff[(size_t)p];
     const int32_t din = c->dims[(size_t)layer - 1], dout = c->dims[(size_t)layer];
     const char* W = c->w[(size_t)3 * (layer - 1)];
     float* gW = c->gw[(size_t)3 * (layer - 1)];
@@ -647,15 +688,16 @@ const char* compute_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own
         Timed t(c, s, GNN_K_ACT_BWD);
         if (b16) {
             launch_act_bwd_bf16(g_own, layer < L ? act_own : nullptr, dYbuf, np, dout, gb, colpart,
-                                drop_scale, s);
+                                drop_scale, s, row_blocks(c));
             dY = dYbuf;
         } else if (layer < L) {
-            launch_act_bwd(g_own, (const float*)act_own, (float*)dYbuf, np, dout, gb, colpart, drop_scale, s);
+            launch_act_bwd(g_own, (const float*)act_own, (float*)dYbuf, np, dout, gb, colpart, drop_scale, s, nullptr,
+                           row_blocks(c));
             dY = dYbuf;
         } else {
             // output layer: grad A^L is the loss kernel's, zero outside the train mask
             launch_act_bwd(g_own, nullptr, nullptr, np, dout, gb, colpart, 1.f, s,
-                           c->streaming() ? nullptr : c->mask + M.off[(size_t)p]);
+                           c->streaming() ? nullptr : c->mask + M.off[(size_t)p], row_blocks(c));
         }
     }
     // recompute the aggregate from the regathered rows (unless the forward pass's is kept)
@@ -664,15 +706,8 @@ const char* compute_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own
     // weight gradients, summed over partitions
     {
         Timed t(c, s, GNN_K_GEMM_DW);
-        if (b16) {
-            launch_gemm_bf16_tn(Z, din, dY, dout, gW, dout, din, dout, np, partial, s);
-            if (sage) launch_gemm_bf16_tn(in_own, din, dY, dout, gWs, dout, din, dout, np, partial, s);
-        } else {
-            launch_gemm_tn((const float*)Z, din, (const float*)dY, dout, gW, dout, din, dout, np, partial, s);
-            if (sage)
-                launch_gemm_tn((const float*)in_own, din, (const float*)dY, dout, gWs, dout, din, dout, np,
-                               partial, s);
-        }
+        weight_grad(c, Z, din, dY, dout, gW, dout, din, dout, np, partial, s);
+        if (sage) weight_grad(c, in_own, din, dY, dout, gWs, dout, din, dout, np, partial, s);
     }
     if (layer >= 2) {
         {
@@ -680,6 +715,13 @@ const char* compute_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own
             GemmEpilogue ep;
             if (b16) launch_gemm_bf16_nt(dY, dout, W, dout, dZ, 1, din, np, din, dout, ep, s);
             else launch_gemm_nt((const float*)dY, dout, (const float*)W, dout, (float*)dZ, din, np, din, dout, ep, s);
+        }
+        if (c->merged_transpose()) {
+            // every partition at once: a row of grad A^{l-1} is stored once, the self term of its
+            // own partition joining the sum where that partition's turn comes
+            if (sage) compute_bwd_self(c, layer, p, dY, fused_gprev, s, 0);
+            run_spmm_merged(c, layer, dZ, fused_gprev, din, sage ? 1 : 0, s);
+            return dY;
         }
         float* segpart = (float*)(c->scratch + c->ws.segpart);
         // With fused_gprev the transposed aggregation adds each row of the gathered-row gradient
@@ -761,7 +803,7 @@ void xf_aggregate_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, 
     const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
     const int32_t din = c->dims[(size_t)layer - 1], dout = c->dims[(size_t)layer], dp = c->padded(layer);
     SpmmItems items = plan_items(M.plan_fwd, c->D.fwd, p);
-    items.avg_len = (float)(M.rp[(size_t)M.off[(size_t)p + 1]] - M.rp[(size_t)r0]) / (float)std::max<int64_t>(1, np);
+    items.avg_len = entries_per_row(M, p);
     const float* rscale = c->D.rscale ? c->D.rscale + r0 : nullptr;
     float* Z = (float*)(c->scratch + c->ws.z);
     float* segpart = (float*)(c->scratch + c->ws.segpart);
@@ -841,7 +883,6 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
     const HostMeta& M = c->M;
     const int32_t L = c->L;
     const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
-    const int64_t nb = M.boff[(size_t)p + 1] - M.boff[(size_t)p];
     const int32_t din = c->dims[(size_t)layer - 1], dout = c->dims[(size_t)layer], dp = c->padded(layer);
     float* gb = c->has_bias ? c->gw[(size_t)3 * (layer - 1) + 2] : nullptr;
     float* dYbuf = (float*)(c->scratch + c->ws.dy);
@@ -852,17 +893,21 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
         {
             Timed t(c, s, GNN_K_ACT_BWD);
             launch_act_bwd_bf16(g_own, layer < L ? act_own : nullptr, dYbuf, np, dout, gb, colpart,
-                                layer < L ? drop_scale : 1.f, s);
+                                layer < L ? drop_scale : 1.f, s, row_blocks(c));
         }
         if (c->model == GNN_SAGE_MEAN) {
             {
                 Timed t(c, s, GNN_K_GEMM_DW);
-                launch_gemm_bf16_tn(in_own_c, din, dYbuf, dout, c->gw[(size_t)3 * (layer - 1) + 1],
-                                    dout, din, dout, np, (float*)(c->scratch + c->ws.partial), s);
+                weight_grad(c, in_own_c, din, dYbuf, dout, c->gw[(size_t)3 * (layer - 1) + 1],
+                            dout, din, dout, np, (float*)(c->scratch + c->ws.partial), s);
             }
             if (layer >= 2)
                 // (the first thing written to these rows of grad A^{l-1})
                 compute_bwd_self(c, layer, p, (const char*)dYbuf, gprev_own, s, 0);
+        }
+        if (c->merged_transpose()) {
+            run_spmm_merged(c, layer, dYbuf, (float*)c->ghbuf, dp, 0, s);
+            return;
         }
         const TransposedOp opb = transposed_op(c, layer, p);
         float* segb = (float*)(c->scratch + c->ws.segpart);
@@ -887,12 +932,12 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
         Timed t(c, s, GNN_K_ACT_BWD);
         if (layer < L) {
             launch_act_bwd(g_own, (const float*)act_own, dYbuf, np, dout, gb,
-                           colpart, drop_scale, s);
+                           colpart, drop_scale, s, nullptr, row_blocks(c));
             dY = dYbuf;
         } else {
             // output layer: grad A^L is the loss kernel's, zero outside the train mask
             launch_act_bwd(g_own, nullptr, nullptr, np, dout, gb, colpart, 1.f, s,
-                           c->streaming() ? nullptr : c->mask + r0);
+                           c->streaming() ? nullptr : c->mask + r0, row_blocks(c));
         }
     }
     const float* in_own = (const float*)in_own_c;
@@ -907,8 +952,8 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
     if (c->model == GNN_SAGE_MEAN) {
         {
             Timed t(c, s, GNN_K_GEMM_DW);
-            launch_gemm_tn(in_own, din, dYp, dp, c->gw[(size_t)3 * (layer - 1) + 1], dout, din, dout, np,
-                           (float*)(c->scratch + c->ws.partial), s);
+            weight_grad(c, in_own, din, dYp, dp, c->gw[(size_t)3 * (layer - 1) + 1], dout, din, dout, np,
+                        (float*)(c->scratch + c->ws.partial), s);
         }
         if (layer >= 2 && layer < L && !keep && gprev_own) {
             // self term: grad A^{l-1}_own = dY W_s^T (the first thing written to these rows),
@@ -921,9 +966,13 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
             launch_gemm_nt(dYp, dp, ws.p, ws.ld, gprev_own, din, np, din, dp, ep, s);
         }
     }
+    float* gH = (float*)c->ghbuf;
+    if (c->merged_transpose()) {
+        run_spmm_merged(c, layer, dYp, gH, dp, 0, s);
+        return;
+    }
     const TransposedOp op = transposed_op(c, layer, p);
     float* segpart = (float*)(c->scratch + c->ws.segpart);
-    float* gH = (float*)c->ghbuf;
     {
         Timed t(c, s, GNN_K_SPMM_T);
         launch_spmm(op.rp, op.col, op.w, nullptr, dYp, np, nullptr, gH, op.nrows, dp, 0, 0, op.items,
@@ -984,8 +1033,8 @@ void xf_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
         }
         {
             Timed t(c, s, GNN_K_GEMM_DW);
-            launch_gemm_bf16_tn(in_own_c, din, gHb, dp, c->gw[(size_t)3 * (layer - 1)], dout, din,
-                                dout, np, (float*)(c->scratch + c->ws.partial), s);
+            weight_grad(c, in_own_c, din, gHb, dp, c->gw[(size_t)3 * (layer - 1)], dout, din,
+                        dout, np, (float*)(c->scratch + c->ws.partial), s);
         }
         if (layer >= 2) {
             Timed t(c, s, GNN_K_GEMM_DZ);
@@ -999,8 +1048,8 @@ void xf_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own_c
     const float* in_own = (const float*)in_own_c;
     {
         Timed t(c, s, GNN_K_GEMM_DW);
-        launch_gemm_tn(in_own, din, gH, dp, c->gw[(size_t)3 * (layer - 1)], dout, din, dout, np,
-                       (float*)(c->scratch + (c->on_side ? c->ws.partial2 : c->ws.partial)), s);
+        weight_grad(c, in_own, din, gH, dp, c->gw[(size_t)3 * (layer - 1)], dout, din, dout, np,
+                    (float*)(c->scratch + (c->on_side ? c->ws.partial2 : c->ws.partial)), s);
     }
     const float* dYk = nullptr;          // padded dY_p of a hidden GraphSAGE layer
     if (c->model == GNN_SAGE_MEAN && layer >= 2 && layer < c->L) {
@@ -1053,7 +1102,8 @@ void xf_begin_bwd(gnn_ctx* c, int32_t layer, hipStream_t s)
 {
     // (an epoch that lets first-touch rows store has nothing to zero, unless the operator is the
     // output layer's over train vertices, which does not reach every row)
-    if (!(c->first_touch && c->D.first && !(layer == c->L && c->masked_transpose()))) {
+    // (neither has the whole-graph operator, which stores every row)
+    if (!c->merged_transpose() && !(c->first_touch && c->D.first && !(layer == c->L && c->masked_transpose()))) {
         Timed t(c, s, GNN_K_OTHER);
         launch_fill_zero(c->ghbuf, c->M.n * (int64_t)c->padded(layer) * 4, s);
         // grad A^{l-1} needs no initialisation here: each of its rows is written once (by
@@ -1100,6 +1150,7 @@ void gnn_destroy(gnn_ctx* c)
     if (!c) return;
     stream_engine_destroy(c);
     tier_close(c);
+    whole_free(c);
     if (c->D.ready) free_device(c->D);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->side_events) (void)hipEventDestroy(e);
@@ -1123,6 +1174,7 @@ gnn_status gnn_build_partitions(gnn_ctx* c, int64_t n, const int64_t* rowptr, co
         if (st != GNN_OK) return c->fail(st, err);
         stream_engine_destroy(c);
         tier_close(c);                 // its arrays were sized for the graph before
+        whole_free(c);
         if (c->D.ready) free_device(c->D);
         c->M = std::move(M);
     } catch (const std::bad_alloc&) {
@@ -1286,6 +1338,7 @@ gnn_status gnn_bind(gnn_ctx* c, const void* feat, void* const* act, void* const*
         if (st != GNN_OK) return st;
     }
     c->bound = true;
+    whole_bind(c);
     return GNN_OK;
 }
 
@@ -1352,8 +1405,10 @@ gnn_status gnn_set_gather_fusion(gnn_ctx* c, int32_t on)
     if (on != 0 && on != 1) return c->fail(GNN_EINVAL, "gnn_set_gather_fusion takes 0 or 1");
     c->fuse_gather = on == 1;
     c->staged_layer = c->staged_p = -1;       // staging holds nothing the other mode could use
-    if (c->fuse_gather && c->D.ready && !c->streaming()) return ensure_global_columns(c);
-    return GNN_OK;
+    gnn_status st = GNN_OK;
+    if (c->fuse_gather && c->D.ready && !c->streaming()) st = ensure_global_columns(c);
+    if (st == GNN_OK && c->bound) whole_update(c);
+    return st;
 }
 
 gnn_status gnn_set_masked_backward(gnn_ctx* c, int32_t on)
@@ -1361,12 +1416,11 @@ gnn_status gnn_set_masked_backward(gnn_ctx* c, int32_t on)
     if (!c) return GNN_EINVAL;
     if (on != 0 && on != 1) return c->fail(GNN_EINVAL, "gnn_set_masked_backward takes 0 or 1");
     c->masked_bwd = on == 1;
-    if (!c->masked_bwd) {
-        free_masked(c->D.masked_t);
-        return GNN_OK;
-    }
-    if (c->bound && !c->streaming() && c->model != GNN_GAT && !c->D.masked_t.ready) return build_masked(c);
-    return GNN_OK;
+    gnn_status st = GNN_OK;
+    if (!c->masked_bwd) free_masked(c->D.masked_t);
+    else if (c->bound && !c->streaming() && c->model != GNN_GAT && !c->D.masked_t.ready) st = build_masked(c);
+    if (st == GNN_OK && c->bound) whole_update(c);
+    return st;
 }
 
 gnn_status gnn_get_masked_backward_size(const gnn_ctx* c, int64_t* entries, int64_t* rows)
@@ -1516,9 +1570,14 @@ gnn_status gnn_loss(gnn_ctx* c, void* stream)
     float* scal = (float*)(c->scratch + c->ws.scalars);
     {
         Timed t(c, s, GNN_K_LOSS);
-        launch_loss((const float*)c->act[(size_t)c->L - 1], c->labels, c->mask, c->gact[(size_t)c->L - 1],
-                    c->M.n, c->dims[(size_t)c->L], c->M.off.data(), c->M.k, (unsigned long long*)(scal + 16),
-                    (float*)(c->scratch + c->ws.losspart), scal, s);
+        if (c->is_whole)
+            launch_loss_blocks((const float*)c->act[(size_t)c->L - 1], c->labels, c->mask, c->gact[(size_t)c->L - 1],
+                               c->M.n, c->dims[(size_t)c->L], c->tables.rb, (unsigned long long*)(scal + 16),
+                               (float*)(c->scratch + c->ws.losspart), scal, s);
+        else
+            launch_loss((const float*)c->act[(size_t)c->L - 1], c->labels, c->mask, c->gact[(size_t)c->L - 1],
+                        c->M.n, c->dims[(size_t)c->L], c->M.off.data(), c->M.k, (unsigned long long*)(scal + 16),
+                        (float*)(c->scratch + c->ws.losspart), scal, s);
     }
     c->loss_done = true;
     std::fill(c->bwd_done.begin(), c->bwd_done.end(), 0);
@@ -1621,7 +1680,8 @@ gnn_status gnn_layer_bwd(gnn_ctx* c, int32_t layer, int32_t p, void* stream)
     // write-back buffer initialisation: first partition of this layer since gnn_loss (not when
     // the epoch lets first-touch rows store; the operator over train vertices does not reach
     // every row)
-    const bool stores_first = fuse && c->first_touch && c->D.first && !(layer == c->L && c->masked_transpose());
+    const bool stores_first = c->merged_transpose() ||
+                              (fuse && c->first_touch && c->D.first && !(layer == c->L && c->masked_transpose()));
     if (layer >= 2 && c->bwd_done[(size_t)layer] == 0 && !stores_first) {
         Timed t(c, s, GNN_K_OTHER);
         launch_fill_zero(c->gact[(size_t)layer - 2], M.n * (int64_t)din * 4, s);
@@ -1629,8 +1689,9 @@ gnn_status gnn_layer_bwd(gnn_ctx* c, int32_t layer, int32_t p, void* stream)
     const char* act_own = c->act[(size_t)layer - 1] + r0 * (int64_t)dout * c->act_es(layer);
     float* gprev = layer >= 2 ? c->gact[(size_t)layer - 2] : nullptr;
     const char* dY = compute_bwd(c, layer, p, c->layer_input(layer, r0),
-                                 c->gact[(size_t)layer - 1] + r0 * dout, act_own, fuse ? gprev : nullptr, nullptr, s);
-    if (layer >= 2) {
+                                 c->gact[(size_t)layer - 1] + r0 * dout, act_own,
+                                 fuse || c->merged_transpose() ? gprev : nullptr, nullptr, s);
+    if (layer >= 2 && !c->merged_transpose()) {
         if (!fuse) {
             Timed t(c, s, GNN_K_SCATTER);
             launch_scatter_add((const float*)(c->scratch + c->ws.dga), np + nb, np, r0,
@@ -1642,8 +1703,6 @@ gnn_status gnn_layer_bwd(gnn_ctx* c, int32_t layer, int32_t p, void* stream)
     return check_launch(c, "gnn_layer_bwd");
 }
 
-static gnn_status epoch_resident(gnn_ctx* c, void* stream, float* loss_out);
-
 gnn_status gnn_epoch(gnn_ctx* c, void* stream, float* loss_out)
 {
     if (!c || !loss_out) return GNN_EINVAL;
@@ -1654,6 +1713,7 @@ gnn_status gnn_epoch(gnn_ctx* c, void* stream, float* loss_out)
         if (st == GNN_OK && c->prof) collect_profile(c);
         return st;
     }
+    if (whole_runs(c)) return whole_epoch(c, stream, loss_out);
     const gnn_status st = epoch_resident(c, stream, loss_out);
     if (st != GNN_OK) {
         // an error exit may leave work queued on the context's side stream: the caller's stream
@@ -1668,151 +1728,6 @@ gnn_status gnn_epoch(gnn_ctx* c, void* stream, float* loss_out)
         }
     }
     return st;
-}
-
-static gnn_status epoch_resident(gnn_ctx* c, void* stream, float* loss_out)
-{
-    hipStream_t s = (hipStream_t)stream;
-    const int32_t L = c->L, k = c->M.k;
-    gnn_status st = GNN_OK;
-    // Overlap (fp32 GCN / GraphSAGE): where an aggregate-first layer l sits below a transform-first
-    // layer l + 1, the contractions of layer l + 1's own sweep (H_p = A_p^l W forward; grad W,
-    // grad A_p^l backward) run on a side stream, partition by partition, beside layer l's gather /
-    // aggregation kernels of the other partitions.  Those contractions touch only rows of
-    // partition p, H / grad H, the padded weight copies, their own weight gradient and a split-K
-    // region of their own; every dependency is an event, and each buffer sees its kernels in the
-    // order of the one-stream schedule, so the results are the same bits.  GNNMI_OVERLAP=0: off.
-    const char* overlap_env = std::getenv("GNNMI_OVERLAP");          // read per epoch: tests flip it
-    bool overlap = !(overlap_env && overlap_env[0] == '0') && !c->bf16() && c->model != GNN_GAT;
-    if (overlap) {
-        bool any = false;                 // an aggregate-first layer: its forward contraction moves too
-        for (int32_t l = 1; l <= L; ++l) any = any || !c->transform_first(l);
-        overlap = any;
-    }
-    if (overlap && !c->side) {
-        if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
-            (void)hipGetLastError();
-            c->side = nullptr;
-            overlap = false;
-        }
-    }
-    if (overlap)
-        while (c->side_events.size() < (size_t)k + 5) {   // k steps, two fences, Z ready, two Z regions free
-            hipEvent_t e;
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-                (void)hipGetLastError();
-                overlap = false;
-                break;
-            }
-            c->side_events.push_back(e);
-        }
-    // layer l aggregates first and layer l + 1 transforms first
-    auto paired = [&](int32_t l) {
-        return overlap && l >= 1 && l < L && !c->transform_first(l) && c->transform_first(l + 1);
-    };
-    // backward: a GraphSAGE output layer with padded rows pads its dY into scratch that layer l's
-    // partitions use as well, so that pair stays on one stream
-    auto paired_bwd = [&](int32_t l) {
-        return paired(l) && !(c->model == GNN_SAGE_MEAN && l + 1 == L && c->padded(L) != c->dims[(size_t)L]);
-    };
-    auto hip_ok = [&](hipError_t e, const char* what) {
-        if (e == hipSuccess) return GNN_OK;
-        return c->fail(GNN_EHIP, std::string(what) + ": " + hipGetErrorString(e));
-    };
-    hipEvent_t* step_event = c->side_events.data();                          // [k]
-    const hipEvent_t fence_main = overlap ? c->side_events[(size_t)k] : nullptr;
-    const hipEvent_t fence_side = overlap ? c->side_events[(size_t)k + 1] : nullptr;
-
-    zero_weight_grads(c, s);
-    for (int32_t l = 1; l <= L; ++l) {
-        if (c->transform_first(l) && !paired(l - 1))
-            for (int32_t t = 0; t < k; ++t)
-                if ((st = gnn_layer_transform_fwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
-        // an aggregate-first layer: Z_p is aggregated on the caller's stream into one of two
-        // regions and its contraction follows on the side stream while the caller's stream
-        // gathers and aggregates the next partition
-        // (not when layer l + 1 keeps the side stream busy already: measured neutral in wall time
-        // there, and it only stretches the aggregation kernels further)
-        const bool side_fwd = overlap && !c->transform_first(l) && !paired(l);
-        for (int32_t t = 0; t < k; ++t) {
-            const int32_t p = c->M.sched[(size_t)t];
-            if (side_fwd) {
-                c->z_slot = t & 1;
-                // the contraction that read this region two steps ago
-                const hipEvent_t z_free = c->side_events[c->side_events.size() - 2 + (size_t)c->z_slot];
-                if ((st = hip_ok(hipStreamWaitEvent(s, z_free, 0), "hipStreamWaitEvent")) != GNN_OK) break;
-                c->fwd_side = c->side;
-            }
-            if ((st = gnn_gather_boundary(c, l, p, stream)) != GNN_OK) break;
-            if ((st = gnn_layer_fwd(c, l, p, stream)) != GNN_OK) break;
-            if (paired(l)) {
-                // A_p^l is complete on the caller's stream: layer l + 1 transforms it on the side
-                if ((st = hip_ok(hipEventRecord(step_event[t], s), "hipEventRecord")) != GNN_OK) break;
-                if ((st = hip_ok(hipStreamWaitEvent(c->side, step_event[t], 0), "hipStreamWaitEvent")) != GNN_OK) break;
-                if ((st = gnn_layer_transform_fwd(c, l + 1, p, (void*)c->side)) != GNN_OK) break;
-            }
-        }
-        c->fwd_side = nullptr;
-        c->z_slot = 0;
-        if (st != GNN_OK) return st;
-        if (side_fwd || paired(l)) {
-            if ((st = hip_ok(hipEventRecord(fence_side, c->side), "hipEventRecord")) != GNN_OK) return st;
-            if ((st = hip_ok(hipStreamWaitEvent(s, fence_side, 0), "hipStreamWaitEvent")) != GNN_OK) return st;
-        }
-    }
-    if ((st = gnn_loss(c, stream)) != GNN_OK) return st;
-    // the partitions of a backward layer are walked in schedule order from here on: rows that are
-    // first to reach their row of a gradient array store, the others add
-    static const bool first_touch_on = [] {
-        const char* e = std::getenv("GNNMI_FIRST_TOUCH");
-        return !(e && e[0] == '0');
-    }();
-    struct FirstTouch {
-        gnn_ctx* c;
-        ~FirstTouch() { c->first_touch = false; }
-    } first_touch_scope{c};
-    c->first_touch = first_touch_on && c->model != GNN_GAT;
-    bool wait_steps = false;          // the partitions of this layer wait for the side stream, step by step
-    for (int32_t l = L; l >= 1; --l) {
-        const bool xf = c->transform_first(l);
-        const bool regather = !xf || c->model == GNN_GAT;
-        if (c->model == GNN_GAT && c->h_layer != l &&
-            !(c->keep_forward && all_done(c->xf_fwd_done, l, k) == k))
-            // attention needs H and the scores of this layer again: recompute them
-            for (int32_t t = 0; t < k; ++t)
-                if ((st = gnn_layer_transform_fwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
-        for (int32_t t = 0; t < k; ++t) {
-            const int32_t p = c->M.sched[(size_t)t];
-            if (wait_steps &&
-                (st = hip_ok(hipStreamWaitEvent(s, step_event[t], 0), "hipStreamWaitEvent")) != GNN_OK)
-                return st;
-            const bool kept = c->keeps_z(l) && c->z_done[(size_t)(l - 1) * (size_t)k + (size_t)p];
-            if (regather && !kept && (st = gnn_gather_boundary(c, l, p, stream)) != GNN_OK) return st;
-            if ((st = gnn_layer_bwd(c, l, p, stream)) != GNN_OK) return st;
-        }
-        wait_steps = false;
-        if (xf && paired_bwd(l - 1)) {
-            // grad H of this layer is complete on the caller's stream: its contractions go to the
-            // side stream, and partition p of layer l - 1 starts when grad A_p^{l-1} is there
-            if ((st = hip_ok(hipEventRecord(fence_main, s), "hipEventRecord")) != GNN_OK) return st;
-            if ((st = hip_ok(hipStreamWaitEvent(c->side, fence_main, 0), "hipStreamWaitEvent")) != GNN_OK) return st;
-            c->on_side = true;
-            for (int32_t t = 0; t < k; ++t) {
-                st = gnn_layer_transform_bwd(c, l, c->M.sched[(size_t)t], (void*)c->side);
-                if (st == GNN_OK) st = hip_ok(hipEventRecord(step_event[t], c->side), "hipEventRecord");
-                if (st != GNN_OK) break;
-            }
-            c->on_side = false;
-            if (st != GNN_OK) return st;
-            wait_steps = true;
-        } else if (xf) {
-            for (int32_t t = 0; t < k; ++t)
-                if ((st = gnn_layer_transform_bwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
-        }
-    }
-    if ((st = gnn_read_loss(c, stream, loss_out)) != GNN_OK) return st;
-    if (c->prof) collect_profile(c);
-    return GNN_OK;
 }
 
 gnn_status gnn_set_dropout(gnn_ctx* c, float p, uint64_t seed, int64_t epoch_index)
@@ -2009,3 +1924,152 @@ gnn_status gnn_get_stream_stats(const gnn_ctx* c, gnn_stream_stats* out)
 }
 
 }  // extern "C"
+
+namespace gnnmi {
+
+gnn_status epoch_resident(gnn_ctx* c, void* stream, float* loss_out)
+{
+    hipStream_t s = (hipStream_t)stream;
+    const int32_t L = c->L, k = c->M.k;
+    gnn_status st = GNN_OK;
+    // Overlap (fp32 GCN / GraphSAGE): where an aggregate-first layer l sits below a transform-first
+    // layer l + 1, the contractions of layer l + 1's own sweep (H_p = A_p^l W forward; grad W,
+    // grad A_p^l backward) run on a side stream, partition by partition, beside layer l's gather /
+    // aggregation kernels of the other partitions.  Those contractions touch only rows of
+    // partition p, H / grad H, the padded weight copies, their own weight gradient and a split-K
+    // region of their own; every dependency is an event, and each buffer sees its kernels in the
+    // order of the one-stream schedule, so the results are the same bits.  GNNMI_OVERLAP=0: off.
+    const char* overlap_env = std::getenv("GNNMI_OVERLAP");          // read per epoch: tests flip it
+    bool overlap = !(overlap_env && overlap_env[0] == '0') && !c->bf16() && c->model != GNN_GAT && !c->is_whole;
+    if (overlap) {
+        bool any = false;                 // an aggregate-first layer: its forward contraction moves too
+        for (int32_t l = 1; l <= L; ++l) any = any || !c->transform_first(l);
+        overlap = any;
+    }
+    if (overlap && !c->side) {
+        if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
+            (void)hipGetLastError();
+            c->side = nullptr;
+            overlap = false;
+        }
+    }
+    if (overlap)
+        while (c->side_events.size() < (size_t)k + 5) {   // k steps, two fences, Z ready, two Z regions free
+            hipEvent_t e;
+            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                overlap = false;
+                break;
+            }
+            c->side_events.push_back(e);
+        }
+    // layer l aggregates first and layer l + 1 transforms first
+    auto paired = [&](int32_t l) {
+        return overlap && l >= 1 && l < L && !c->transform_first(l) && c->transform_first(l + 1);
+    };
+    // backward: a GraphSAGE output layer with padded rows pads its dY into scratch that layer l's
+    // partitions use as well, so that pair stays on one stream
+    auto paired_bwd = [&](int32_t l) {
+        return paired(l) && !(c->model == GNN_SAGE_MEAN && l + 1 == L && c->padded(L) != c->dims[(size_t)L]);
+    };
+    auto hip_ok = [&](hipError_t e, const char* what) {
+        if (e == hipSuccess) return GNN_OK;
+        return c->fail(GNN_EHIP, std::string(what) + ": " + hipGetErrorString(e));
+    };
+    hipEvent_t* step_event = c->side_events.data();                          // [k]
+    const hipEvent_t fence_main = overlap ? c->side_events[(size_t)k] : nullptr;
+    const hipEvent_t fence_side = overlap ? c->side_events[(size_t)k + 1] : nullptr;
+
+    zero_weight_grads(c, s);
+    for (int32_t l = 1; l <= L; ++l) {
+        if (c->transform_first(l) && !paired(l - 1))
+            for (int32_t t = 0; t < k; ++t)
+                if ((st = gnn_layer_transform_fwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
+        // an aggregate-first layer: Z_p is aggregated on the caller's stream into one of two
+        // regions and its contraction follows on the side stream while the caller's stream
+        // gathers and aggregates the next partition
+        // (not when layer l + 1 keeps the side stream busy already: measured neutral in wall time
+        // there, and it only stretches the aggregation kernels further)
+        const bool side_fwd = overlap && !c->transform_first(l) && !paired(l);
+        for (int32_t t = 0; t < k; ++t) {
+            const int32_t p = c->M.sched[(size_t)t];
+            if (side_fwd) {
+                c->z_slot = t & 1;
+                // the contraction that read this region two steps ago
+                const hipEvent_t z_free = c->side_events[c->side_events.size() - 2 + (size_t)c->z_slot];
+                if ((st = hip_ok(hipStreamWaitEvent(s, z_free, 0), "hipStreamWaitEvent")) != GNN_OK) break;
+                c->fwd_side = c->side;
+            }
+            if ((st = gnn_gather_boundary(c, l, p, stream)) != GNN_OK) break;
+            if ((st = gnn_layer_fwd(c, l, p, stream)) != GNN_OK) break;
+            if (paired(l)) {
+                // A_p^l is complete on the caller's stream: layer l + 1 transforms it on the side
+                if ((st = hip_ok(hipEventRecord(step_event[t], s), "hipEventRecord")) != GNN_OK) break;
+                if ((st = hip_ok(hipStreamWaitEvent(c->side, step_event[t], 0), "hipStreamWaitEvent")) != GNN_OK) break;
+                if ((st = gnn_layer_transform_fwd(c, l + 1, p, (void*)c->side)) != GNN_OK) break;
+            }
+        }
+        c->fwd_side = nullptr;
+        c->z_slot = 0;
+        if (st != GNN_OK) return st;
+        if (side_fwd || paired(l)) {
+            if ((st = hip_ok(hipEventRecord(fence_side, c->side), "hipEventRecord")) != GNN_OK) return st;
+            if ((st = hip_ok(hipStreamWaitEvent(s, fence_side, 0), "hipStreamWaitEvent")) != GNN_OK) return st;
+        }
+    }
+    if ((st = gnn_loss(c, stream)) != GNN_OK) return st;
+    // the partitions of a backward layer are walked in schedule order from here on: rows that are
+    // first to reach their row of a gradient array store, the others add
+    static const bool first_touch_on = [] {
+        const char* e = std::getenv("GNNMI_FIRST_TOUCH");
+        return !(e && e[0] == '0');
+    }();
+    struct FirstTouch {
+        gnn_ctx* c;
+        ~FirstTouch() { c->first_touch = false; }
+    } first_touch_scope{c};
+    c->first_touch = first_touch_on && c->model != GNN_GAT;
+    bool wait_steps = false;          // the partitions of this layer wait for the side stream, step by step
+    for (int32_t l = L; l >= 1; --l) {
+        const bool xf = c->transform_first(l);
+        const bool regather = !xf || c->model == GNN_GAT;
+        if (c->model == GNN_GAT && c->h_layer != l &&
+            !(c->keep_forward && all_done(c->xf_fwd_done, l, k) == k))
+            // attention needs H and the scores of this layer again: recompute them
+            for (int32_t t = 0; t < k; ++t)
+                if ((st = gnn_layer_transform_fwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
+        for (int32_t t = 0; t < k; ++t) {
+            const int32_t p = c->M.sched[(size_t)t];
+            if (wait_steps &&
+                (st = hip_ok(hipStreamWaitEvent(s, step_event[t], 0), "hipStreamWaitEvent")) != GNN_OK)
+                return st;
+            const bool kept = c->keeps_z(l) && c->z_done[(size_t)(l - 1) * (size_t)k + (size_t)p];
+            if (regather && !kept && (st = gnn_gather_boundary(c, l, p, stream)) != GNN_OK) return st;
+            if ((st = gnn_layer_bwd(c, l, p, stream)) != GNN_OK) return st;
+        }
+        wait_steps = false;
+        if (xf && paired_bwd(l - 1)) {
+            // grad H of this layer is complete on the caller's stream: its contractions go to the
+            // side stream, and partition p of layer l - 1 starts when grad A_p^{l-1} is there
+            if ((st = hip_ok(hipEventRecord(fence_main, s), "hipEventRecord")) != GNN_OK) return st;
+            if ((st = hip_ok(hipStreamWaitEvent(c->side, fence_main, 0), "hipStreamWaitEvent")) != GNN_OK) return st;
+            c->on_side = true;
+            for (int32_t t = 0; t < k; ++t) {
+                st = gnn_layer_transform_bwd(c, l, c->M.sched[(size_t)t], (void*)c->side);
+                if (st == GNN_OK) st = hip_ok(hipEventRecord(step_event[t], c->side), "hipEventRecord");
+                if (st != GNN_OK) break;
+            }
+            c->on_side = false;
+            if (st != GNN_OK) return st;
+            wait_steps = true;
+        } else if (xf) {
+            for (int32_t t = 0; t < k; ++t)
+                if ((st = gnn_layer_transform_bwd(c, l, c->M.sched[(size_t)t], stream)) != GNN_OK) return st;
+        }
+    }
+    if ((st = gnn_read_loss(c, stream, loss_out)) != GNN_OK) return st;
+    if (c->prof) collect_profile(c);
+    return GNN_OK;
+}
+
+}  // namespace gnnmi

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <map>
 #include <memory>
 #include <string>
 #include <vector>
@@ -45,6 +46,23 @@ struct DevMeta {
         Plan plan;
         bool ready = false;
     } masked_t;
+    // whole-graph transposed operator (MergedItems), and the same over train vertices
+    struct Merged {
+        int64_t* rp = nullptr;
+        int32_t* col = nullptr;
+        float* w = nullptr;
+        int32_t* rows = nullptr;
+        int64_t* unit_begin = nullptr;
+        int32_t* unit_len = nullptr;
+        int32_t* long_row = nullptr;
+        int32_t* long_first = nullptr;
+        int32_t* long_nunits = nullptr;
+        float* partial = nullptr;
+        uint8_t* self_first = nullptr;
+        int64_t nrows = 0, nunits = 0, nlong = 0, entries = 0;
+        float avg_len = 0.f;
+        bool ready = false;
+    } merged, merged_masked;
     bool ready = false;
 };
 
@@ -76,6 +94,14 @@ struct Workspace {  // byte offsets into `scratch`
     // (attention weight, score gradient) pairs of all heads per entry
     int64_t ssrc = 0, sdst = 0, gssrc = 0, gsdst = 0, bs = 0, att = 0, dal = 0, twatt = 0, pair = 0;
     int64_t staging_bytes = 0, scratch_bytes = 0;
+};
+
+// Device tables of the whole-graph schedule: row blocks of the partitions, and per split length the
+// splits of every partition (see TnParts; `wide`: whole stages of 64 rows, `rest`: what they leave).
+struct WholeTables {
+    RowBlocks rb;
+    struct Split { TnParts wide, narrow; };
+    std::map<std::pair<int64_t, int64_t>, Split> splits;   // by (wide chunk or 0, narrow chunk)
 };
 
 struct StreamEngine;  // streaming.cpp
@@ -229,6 +255,18 @@ struct gnn_ctx {
     int z_slot = 0;                        // which Z region compute_fwd uses (0 outside gnn_epoch's forward)
     int64_t z_off() const { return z_slot ? ws.z2 : ws.z; }
 
+    // Whole-graph schedule (whole.cpp): gnn_epoch runs a layer over all partitions at once where the
+    // intermediates fit, through a second context whose one partition is the graph.  It shares this
+    // context's buffers and metadata; results are the bits of the partition-by-partition schedule.
+    gnn_ctx* whole = nullptr;
+    bool is_whole = false;
+    bool whole_ready = false;              // on the outer context: bound and built
+    gnnmi::WholeTables tables;             // on the inner one
+    int32_t parts_k = 0;                   // partitions of the outer context
+    bool whole_staged = false;             // staging holds the boundary rows of all partitions
+    bool merged_transpose() const { return is_whole && D.merged.ready; }
+    int64_t grad_rows() const { return gnnmi::weight_grad_rows(M.n, is_whole ? parts_k : M.k); }
+
     hipError_t deferred = hipSuccess;      // failure of a HIP call inside a void helper, reported by check_launch
 
     gnn_status fail(gnn_status st, const std::string& msg) const
@@ -319,6 +357,26 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, 
                       const char* act_own, float* gprev_own, hipStream_t s);
 void xf_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, const float* g_own,
                       const char* act_own, float* gprev_own, hipStream_t s);
+
+void compute_workspace(gnn_ctx* c);
+gnn_status epoch_resident(gnn_ctx* c, void* stream, float* loss_out);
+// c += A^T B over `rows` rows of one partition (or, in the whole-graph schedule, of all of them,
+// partition by partition), A: rows x m, B: rows x n; fp32, or bfloat16 operands
+void weight_grad(gnn_ctx* c, const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t ldc, int32_t m,
+                 int32_t n, int64_t rows, float* partial, hipStream_t s);
+int64_t weight_grad_partial_floats(const gnn_ctx* c, int32_t m, int32_t n);
+
+// whole.cpp: the whole-graph schedule.  whole_layout: decides whether there is one and sizes the
+// workspace for both schedules; whole_bind / whole_update: (re)builds its metadata after gnn_bind or
+// a changed switch (a failure leaves the partition-by-partition schedule); whole_epoch: one epoch.
+void whole_layout(gnn_ctx* c);
+void whole_bind(gnn_ctx* c);
+void whole_update(gnn_ctx* c);
+void whole_free(gnn_ctx* c);
+bool whole_runs(const gnn_ctx* c);
+gnn_status whole_epoch(gnn_ctx* c, void* stream, float* loss_out);
+// out = rows of the transposed aggregation of `layer` over the whole graph (merged_transpose only)
+void run_spmm_merged(gnn_ctx* c, int32_t layer, const void* src, float* out, int32_t d, int self, hipStream_t s);
 
 void zero_weight_grads(gnn_ctx* c, hipStream_t s);
 SpmmItems plan_items(const HostMeta::Plan& H, const DevMeta::Plan& P, int32_t p);

@@ -182,6 +182,65 @@ void launch_spmm_reduce(const float* rowscale, void* out, int32_t d, int out_bf1
                         const SpmmItems& items, float* partial, const SpmmScatter& sc, hipStream_t s,
                         int32_t ld = 0);
 
+// The transposed operator of the whole graph: row u lists the entries of every partition's T_p^T at
+// vertex u, one partition's after the other's in schedule order (its pieces).  Bit 31 of a column
+// marks the last entry of a piece; bit 30 (GraphSAGE) the entry after which the vertex's own
+// partition has been reached, where the self term joins the sum.  The sum of a row is taken piece by
+// piece - every piece from zero, in segments of `segment` entries where it is longer, then the
+// pieces in order - which is the order in which launches partition by partition accumulate it.
+struct MergedItems {
+    const int64_t* rp = nullptr;
+    const int32_t* col = nullptr;     // destination row | flags
+    const float* w = nullptr;
+    const int32_t* rows = nullptr;    // rows of at most `segment` entries, longest first; top bit: the
+    int64_t nrows = 0;                // self term comes before every piece
+    // longer rows: units (pieces, or segments of a piece) summed on their own and combined per row
+    const int64_t* unit_begin = nullptr;
+    const int32_t* unit_len = nullptr;   // entries | 1 << 31: last of its piece | 1 << 30: self term next
+    int64_t nunits = 0;
+    const int32_t* long_row = nullptr;   // top bit as in rows
+    const int32_t* long_first = nullptr;
+    const int32_t* long_nunits = nullptr;
+    int64_t nlong = 0;
+    float* partial = nullptr;         // nunits rows
+    float avg_len = 0.f;
+};
+constexpr uint32_t kPieceEnd = 0x80000000u, kSelfNext = 0x40000000u;
+constexpr int32_t kMergedColumn = 0x3FFFFFFF;
+// out[u,:] = sum over the entries of row u of w src[col,:] for every row u (fp32 sums; rows d elements
+// apart on both sides).  self: out holds the self term when the kernel starts, which is added
+// where the flags say.
+void launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
+                        int self, hipStream_t s);
+void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s);
+
+// Building it on the device (kernels_merge.hip) from the per-partition transposes.
+// cnt[u] += entries of every row of every T_p^T that belongs to vertex u
+void launch_merge_count(int64_t nrows, int32_t k, const int64_t* toff, const int64_t* off, const int64_t* boff,
+                        const int32_t* bnd, const int64_t* trp, int32_t* cnt, hipStream_t s);
+// appends partition p's piece of every row at cursor[row]; self_first (may be null): marks for
+// GraphSAGE's self term
+void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, const int64_t* trp, const int32_t* tcol,
+                       const float* tw, const int64_t* rp, int64_t* cursor, int32_t* col, float* w,
+                       uint8_t* self_first, hipStream_t s);
+// the operator restricted to destinations with mask != 0: entries kept per row, then the entries
+void launch_merge_mask_count(int64_t n, const int64_t* rp, const int32_t* col, const uint8_t* mask, int32_t* cnt,
+                             hipStream_t s);
+void launch_merge_mask_fill(int64_t n, const int64_t* rp, const int32_t* col, const float* w, const uint8_t* mask,
+                            const int64_t* out_rp, int32_t* out_col, float* out_w, const uint8_t* self_in,
+                            uint8_t* self_out, hipStream_t s);
+// units of the long rows: number per row (begin == null), then the units from first[i] on
+void launch_merge_units(int64_t nlong, const int32_t* long_row, const int64_t* rp, const int32_t* col, int32_t segment,
+                        int32_t* nunits, const int32_t* first, int64_t* begin, int32_t* len, hipStream_t s);
+// list[i] |= 1 << 31 where self_first[list[i]]
+void launch_merge_mark(int32_t* list, int64_t count, const uint8_t* self_first, hipStream_t s);
+// the forward plan's lists with the local row ids of a partition turned into rows of the graph
+void launch_offset_copy(const int32_t* src, int32_t* dst, int64_t count, int32_t add, hipStream_t s);
+// wcol[e] = lcol[e] < n_own ? base + lcol[e] : n + boff + (lcol[e] - n_own): columns of a launch over
+// all partitions whose boundary rows are staged side by side
+void launch_staged_columns(const int32_t* lcol, int32_t* wcol, int64_t count, int64_t n_own, int64_t base, int64_t other,
+                           hipStream_t s);
+
 // dst[map(i),:] += src[i,:] with map(i) = base_row + i for i < n_own, idx[i - n_own] otherwise.
 void launch_scatter_add(const float* src, int64_t nrows, int64_t n_own, int64_t base_row,
                         const int32_t* idx, float* dst, int32_t d, hipStream_t s);
@@ -208,12 +267,45 @@ void launch_gemm_nt(const float* a, int64_t lda, const float* b, int64_t ldb, fl
 // C[M x N] = sum over segments A_seg[M x K_seg] * B_seg^T with B_seg stored [N x K_seg] row-major
 void launch_gemm_nt2(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64_t m, int32_t n,
                      const GemmEpilogue& ep, hipStream_t s);
+// Rows per split of a weight-gradient product A^T B (m x n): about 2048 tiles of 128 x 128 over
+// `rows` rows, 128 to 2048 rows.  `rows` is weight_grad_rows(n, k), a function of the graph and not of
+// the rows of one launch, so that a launch over all partitions splits every partition as a launch of
+// that partition alone does.
+int64_t gemm_tn_chunk(int64_t rows, int32_t m, int32_t n);
+// Graphs small enough for the whole-graph schedule: all rows, so that a partition does not write
+// more partial products than one launch over all partitions needs (64 partitions of 47,000 rows,
+// 128 x 128: 512 splits a partition would write and read 1.5 GB beside 3 GB of operands; 32 do).
+// Larger ones: what a few partitions hold, so that the launch of one fills the chip.
+constexpr int64_t kWholeMaxRows = 6000000;
+inline int64_t weight_grad_rows(int64_t n, int32_t k)
+{
+    return n <= kWholeMaxRows ? n : (n / k) * 4 < n ? (n / k) * 4 : n;
+}
+// The splits of all partitions of a launch over the whole graph, partition after partition in the
+// order their sums are added (device arrays).
+struct TnGroup {
+    int32_t first, count;             // splits of one partition (and kernel)
+    int32_t slot;                     // place of its sum in that order
+};
+struct TnParts {
+    const int2* chunks = nullptr;     // rows [x, y) of every split
+    int32_t nchunks = 0;
+    const TnGroup* groups = nullptr;
+    int32_t ngroups = 0;
+    int32_t nslots = 0;
+};
 // C[M x N] += A^T B with A stored [K x M], B stored [K x N] (K = number of vertices, large):
-// split over K into `splits` partial products in `partial`, then reduced in a fixed order.
-int gemm_tn_splits(int64_t kdim, int32_t m, int32_t n);
+// split over K, `chunk` rows each, into partial products in `partial`, then reduced in a fixed order.
+// parts: the rows are those of several partitions, split and summed partition by partition;
+// `partial` then holds nchunks + nslots matrices.
 void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
-                    int64_t ldc, int32_t m, int32_t n, int64_t kdim, float* partial,
-                    hipStream_t s);
+                    int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t chunk, float* partial,
+                    hipStream_t s, const TnParts* parts = nullptr);
+// sums[slot of group] = sum of the group's splits; c += sums[0], then sums[1], ...
+void launch_reduce_groups(const float* partial, int64_t stride, int32_t m, int32_t n, const TnParts& parts,
+                          float* sums, hipStream_t s);
+void launch_add_groups(const float* sums, int32_t ngroups, int64_t stride, float* c, int64_t ldc, int32_t m, int32_t n,
+                       hipStream_t s);
 
 // bfloat16 operands (raw 16-bit storage), fp32 accumulation; C is fp32 or bfloat16.
 struct GemmSegBf16 {
@@ -231,20 +323,37 @@ void launch_gemm_bf16_nn(const GemmSegBf16* segs, int nseg, void* c, int out_bf1
 void launch_gemm_bf16_nt(const void* a, int64_t lda, const void* b, int64_t ldb, void* c,
                          int out_bf16, int64_t ldc, int64_t m, int32_t n, int32_t k,
                          const GemmEpilogue& ep, hipStream_t s);
-// floats of `partial` a launch_gemm_bf16_tn of these dimensions may use
-int64_t gemm_bf16_tn_partial_floats(int64_t kdim, int32_t m, int32_t n);
+// Weight-gradient products: whole stages of 64 rows of a partition go to the 256 x 256 tile kernel
+// where the matrix is large enough (gemm_bf16_tn_wide_ok; a function of the graph and the widths),
+// gemm_bf16_tn_wide_chunk rows per split, the rest to the narrow kernel, gemm_tn_chunk rows per split.
+bool gemm_bf16_tn_wide_ok(int64_t graph_rows, int32_t m, int32_t n, int64_t lda, int64_t ldb);
+int64_t gemm_bf16_tn_wide_chunk(int64_t graph_rows, int32_t m, int32_t n);
 void launch_gemm_bf16_tn(const void* a, int64_t lda, const void* b, int64_t ldb, float* c,
-                         int64_t ldc, int32_t m, int32_t n, int64_t kdim, float* partial,
-                         hipStream_t s);
+                         int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t graph_rows, float* partial,
+                         hipStream_t s, const TnParts* wide = nullptr, const TnParts* narrow = nullptr);
 // c[i] += sum over splits of partial[split * stride + i], splits in ascending order
 void launch_reduce_partials(const float* partial, int splits, int64_t stride, float* c, int64_t ldc,
                             int32_t m, int32_t n, hipStream_t s);
 void launch_to_bf16(const float* src, void* dst, int64_t n, hipStream_t s);
 
+// Row blocks of a launch over all partitions (device arrays): those of 256 rows of the activation
+// backward with the blocks of every partition in the order their column sums are added, and those of
+// 64 rows of the loss.
+struct RowBlocks {
+    const int2* rows = nullptr;       // rows [x, y) of every block, partition after partition
+    int64_t nblocks = 0;
+    const int2* groups = nullptr;     // first block and number of blocks of a partition
+    int32_t ngroups = 0;
+    const int2* loss_rows = nullptr;
+    int64_t nloss = 0;
+};
+int32_t act_rows_per_block();
+int32_t loss_rows_per_block();
+
 // bfloat16 variant of the activation backward: g fp32, act bfloat16 (or null), dy bfloat16
 // (always written, because the contractions that follow take bfloat16 operands).
 void launch_act_bwd_bf16(const float* g, const void* act, void* dy, int64_t rows, int32_t d,
-                         float* gb, float* partial, float scale, hipStream_t s);
+                         float* gb, float* partial, float scale, hipStream_t s, const RowBlocks* rb = nullptr);
 
 // dy = scale * g * (act > 0) (or dy = g when act == null); colsum partials then gb += colsum.
 // scale = 1 / (1 - p) when dropout followed the activation (the dropped elements are the
@@ -252,8 +361,10 @@ void launch_act_bwd_bf16(const float* g, const void* act, void* dy, int64_t rows
 // `partial` holds ceil(rows / 64) * d floats.
 // row_on (act == null only; may be null): rows with row_on[r] == 0 are known to be zero in g and
 // are not read.
+// rb: the rows are those of all partitions; `partial` then holds nblocks + ngroups rows.
 void launch_act_bwd(const float* g, const float* act, float* dy, int64_t rows, int32_t d,
-                    float* gb, float* partial, float scale, hipStream_t s, const uint8_t* row_on = nullptr);
+                    float* gb, float* partial, float scale, hipStream_t s, const uint8_t* row_on = nullptr,
+                    const RowBlocks* rb = nullptr);
 int64_t act_bwd_partial_floats(int64_t rows, int32_t d);
 
 // softmax cross-entropy over masked rows; grad[n, c]; *loss_dev = mean loss.  count_dev
@@ -263,6 +374,10 @@ void launch_loss(const float* logits, const int32_t* labels, const uint8_t* mask
                  int64_t n, int32_t c, const int64_t* part_off, int32_t k, unsigned long long* count_dev,
                  float* partial, float* loss_dev, hipStream_t s);
 int64_t loss_partial_floats(int64_t n, int32_t k);
+// the same with the row blocks of all partitions in one launch
+void launch_loss_blocks(const float* logits, const int32_t* labels, const uint8_t* mask, float* grad, int64_t n,
+                        int32_t c, const RowBlocks& rb, unsigned long long* count_dev, float* partial,
+                        float* loss_dev, hipStream_t s);
 // the same in three steps, so that the rows can be processed block by block
 void launch_count_mask(const uint8_t* mask, int64_t n, unsigned long long* count_dev, hipStream_t s);
 int64_t launch_loss_rows(const float* logits, const int32_t* labels, const uint8_t* mask, float* grad,

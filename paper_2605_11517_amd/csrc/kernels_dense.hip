@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kBlock) void k_loss(const float* __restrict__ logit
                                                  const uint8_t* __restrict__ mask,
                                                  float* __restrict__ grad, int64_t n, int32_t c,
                                                  const unsigned long long* __restrict__ count,
-                                                 float* __restrict__ partial)
+                                                 float* __restrict__ partial, const int2* __restrict__ blk)
 {
     __shared__ float wsum[kBlock / kWave];
     const unsigned long long cnt = *count;
@@ -40,7 +40,10 @@ __global__ __launch_bounds__(kBlock) void k_loss(const float* __restrict__ logit
     float term = 0.f;
     // the wavefront's rows: their mask bytes in one read, then the zero rows (nothing to wait for,
     // the stores follow each other), then the train rows one by one
-    const int64_t v0 = ((int64_t)blockIdx.x * (kBlock / kWave) + wave) * kLossRowsPerWave;
+    // (blk: the rows of each block, where a launch covers several partitions)
+    const int64_t v0 = (blk ? (int64_t)blk[blockIdx.x].x : (int64_t)blockIdx.x * (kBlock / kWave) * kLossRowsPerWave) +
+                       wave * kLossRowsPerWave;
+    if (blk) n = blk[blockIdx.x].y;
     const bool mine = lane < kLossRowsPerWave && v0 + lane < n;
     const unsigned long long in_range = __ballot(mine);
     const unsigned long long train = __ballot(mine && mask[v0 + lane] != 0);
@@ -158,6 +161,20 @@ __global__ __launch_bounds__(kBlock) void k_loss_finish(const float* __restrict_
     if (threadIdx.x == 0) *loss = sm[0] * inv_count;
 }
 
+// Rows of this block of an activation-backward launch: 256 rows of one partition.  A launch over
+// several partitions lists them (blk), so that the partial sums group the rows as the launches of
+// single partitions do.
+__device__ inline void block_rows(const int2* __restrict__ blk, int64_t rows, int64_t& r0, int64_t& r1)
+{
+    if (blk) {
+        r0 = blk[blockIdx.x].x;
+        r1 = blk[blockIdx.x].y;
+    } else {
+        r0 = (int64_t)blockIdx.x * kRowsPerBlockAct;
+        r1 = r0 + kRowsPerBlockAct < rows ? r0 + kRowsPerBlockAct : rows;
+    }
+}
+
 // dy = scale * g * [act > 0] (act == null: dy aliases g, nothing is written) and per-block column
 // sums of dy into partial[block][d].  A block covers 256 rows.  Up to 256 columns are handled at
 // a time: the block's threads form 256 / width row groups that walk the rows together (four
@@ -166,11 +183,12 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd(const float* __restrict__ g,
                                                     const float* __restrict__ act,
                                                     float* __restrict__ dy, int64_t rows,
                                                     int32_t d, float* __restrict__ partial,
-                                                    float scale, const uint8_t* __restrict__ row_on)
+                                                    float scale, const uint8_t* __restrict__ row_on,
+                                                    const int2* __restrict__ blk)
 {
     __shared__ float sm[kBlock];
-    const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlockAct;
-    const int64_t r1 = r0 + kRowsPerBlockAct < rows ? r0 + kRowsPerBlockAct : rows;
+    int64_t r0, r1;
+    block_rows(blk, rows, r0, r1);
     for (int32_t cc = 0; cc < d; cc += kBlock) {
         const int cwe = d - cc < kBlock ? d - cc : kBlock;     // columns in this chunk
         const int rpp = kBlock / cwe;                          // rows per pass
@@ -218,12 +236,13 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd_vec(const float* __restrict_
                                                         const float* __restrict__ act,
                                                         float* __restrict__ dy, int64_t rows,
                                                         int32_t d, float* __restrict__ partial,
-                                                        float scale, const uint8_t* __restrict__ row_on)
+                                                        float scale, const uint8_t* __restrict__ row_on,
+                                                        const int2* __restrict__ blk)
 {
     __shared__ float4 sm[kBlock];
     const int cw = d / 4;
-    const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlockAct;
-    const int64_t r1 = r0 + kRowsPerBlockAct < rows ? r0 + kRowsPerBlockAct : rows;
+    int64_t r0, r1;
+    block_rows(blk, rows, r0, r1);
     for (int cc = 0; cc < cw; cc += kBlock) {
         const int cwe = cw - cc < kBlock ? cw - cc : kBlock;   // float4 columns in this chunk
         const int rpp = kBlock / cwe;                          // rows per pass
@@ -276,10 +295,10 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd_bf16(const float* __restrict
                                                          const uint16_t* __restrict__ act,
                                                          uint16_t* __restrict__ dy, int64_t rows,
                                                          int32_t d, float* __restrict__ partial,
-                                                         float scale)
+                                                         float scale, const int2* __restrict__ blk)
 {
-    const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlockAct;
-    const int64_t r1 = r0 + kRowsPerBlockAct < rows ? r0 + kRowsPerBlockAct : rows;
+    int64_t r0, r1;
+    block_rows(blk, rows, r0, r1);
     for (int32_t c = threadIdx.x; c < d; c += kBlock) {
         float s = 0.f;
         constexpr int U = 8;
@@ -317,12 +336,12 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd_bf16_vec(const float* __rest
                                                              const uint16_t* __restrict__ act,
                                                              uint16_t* __restrict__ dy, int64_t rows,
                                                              int32_t d, float* __restrict__ partial,
-                                                             float scale)
+                                                             float scale, const int2* __restrict__ blk)
 {
     __shared__ float4 sm[kBlock];
     constexpr int CT = 64, RG = kBlock / CT;               // column threads, row groups
-    const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlockAct;
-    const int64_t r1 = r0 + kRowsPerBlockAct < rows ? r0 + kRowsPerBlockAct : rows;
+    int64_t r0, r1;
+    block_rows(blk, rows, r0, r1);
     const int rsub = threadIdx.x / CT;
     const int32_t c = ((int32_t)blockIdx.y * CT + threadIdx.x % CT) * 4;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -380,9 +399,17 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd_bf16_vec(const float* __rest
 constexpr int kFinishGroups = 32;
 __global__ __launch_bounds__(32 * kFinishGroups) void k_colsum_finish(const float* __restrict__ partial,
                                                                       int64_t nblocks, int32_t d,
-                                                                      float* __restrict__ gb, int32_t ldp)
+                                                                      float* __restrict__ gb, int32_t ldp,
+                                                                      const int2* __restrict__ groups,
+                                                                      float* __restrict__ group_sum)
 {
     __shared__ float sm[kFinishGroups][32];
+    // (groups: one partition's partial rows per blockIdx.y, its sum left in group_sum for
+    // k_add_groups, which adds the partitions in their order)
+    if (groups) {
+        partial += (int64_t)groups[blockIdx.y].x * ldp;
+        nblocks = groups[blockIdx.y].y;
+    }
     const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;
     const int32_t c = blockIdx.x * 32 + tx;
     float s = 0.f;
@@ -401,7 +428,8 @@ __global__ __launch_bounds__(32 * kFinishGroups) void k_colsum_finish(const floa
     __syncthreads();
     if (ty == 0 && c < d) {
         for (int q = 1; q < kFinishGroups; ++q) s += sm[q][tx];
-        gb[c] += s;
+        if (groups) group_sum[(int64_t)blockIdx.y * d + c] = s;
+        else gb[c] += s;
     }
 }
 
@@ -576,7 +604,7 @@ int64_t launch_loss_rows(const float* logits, const int32_t* labels, const uint8
     const int64_t rpb = kLossRowsPerWave * (kBlock / kWave);
     const int64_t blocks = (rows + rpb - 1) / rpb;
     hipLaunchKernelGGL(k_loss, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, labels, mask,
-                       grad, rows, c, count_dev, partial);
+                       grad, rows, c, count_dev, partial, (const int2*)nullptr);
     return blocks;
 }
 
@@ -601,6 +629,19 @@ void launch_loss(const float* logits, const int32_t* labels, const uint8_t* mask
     }
     launch_loss_finish(partial, blocks, count_dev, loss_dev, s);
 }
+
+void launch_loss_blocks(const float* logits, const int32_t* labels, const uint8_t* mask, float* grad, int64_t n,
+                        int32_t c, const RowBlocks& rb, unsigned long long* count_dev, float* partial,
+                        float* loss_dev, hipStream_t s)
+{
+    launch_count_mask(mask, n, count_dev, s);
+    hipLaunchKernelGGL(k_loss, dim3((unsigned)rb.nloss), dim3(kBlock), 0, s, logits, labels, mask, grad, n, c,
+                       count_dev, partial, rb.loss_rows);
+    launch_loss_finish(partial, rb.nloss, count_dev, loss_dev, s);
+}
+
+int32_t loss_rows_per_block() { return kLossRowsPerWave * (kBlock / kWave); }
+int32_t act_rows_per_block() { return kRowsPerBlockAct; }
 
 // ---- loss without a caller workspace --------------------------------------------------------
 // The loss kernels need |M| (8 bytes) and one partial sum per block of 64 rows.  This array
@@ -647,46 +688,60 @@ int64_t act_bwd_partial_floats(int64_t rows, int32_t d)
     return ((rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct) * (int64_t)d;
 }
 
+// gb += column sums of the partial rows: those of one partition, or partition by partition
+static void finish_colsum(const float* partial, int64_t nblocks, int32_t d, float* gb, const RowBlocks* rb,
+                          hipStream_t s)
+{
+    const dim3 block(32 * kFinishGroups);
+    if (rb) {
+        float* sums = const_cast<float*>(partial) + nblocks * d;
+        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32), (unsigned)rb->ngroups), block, 0, s, partial,
+                           nblocks, d, gb, d, rb->groups, sums);
+        launch_add_groups(sums, rb->ngroups, d, gb, d, 1, d, s);
+    } else {
+        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), block, 0, s, partial, nblocks, d, gb, d,
+                           (const int2*)nullptr, (float*)nullptr);
+    }
+}
+
 void launch_act_bwd(const float* g, const float* act, float* dy, int64_t rows, int32_t d,
-                    float* gb, float* partial, float scale, hipStream_t s, const uint8_t* row_on)
+                    float* gb, float* partial, float scale, hipStream_t s, const uint8_t* row_on, const RowBlocks* rb)
 {
     if (!act) scale = 1.f;
     if (act) row_on = nullptr;                  // dy is written for every row
     if (rows <= 0) return;
-    const int64_t blocks = (rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct;
+    const int64_t blocks = rb ? rb->nblocks : (rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct;
+    const int2* blk = rb ? rb->rows : nullptr;
     if (!act && !gb) return;
     const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(act) |
                                      reinterpret_cast<uintptr_t>(dy) |
                                      reinterpret_cast<uintptr_t>(partial)) & 15) == 0;
     if (vec)
         hipLaunchKernelGGL(k_act_bwd_vec, dim3((unsigned)blocks), dim3(kBlock), 0, s, g, act, dy, rows,
-                           d, partial, scale, row_on);
+                           d, partial, scale, row_on, blk);
     else
         hipLaunchKernelGGL(k_act_bwd, dim3((unsigned)blocks), dim3(kBlock), 0, s, g, act, dy, rows, d,
-                           partial, scale, row_on);
-    if (gb)
-        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), dim3(32 * kFinishGroups),
-                           0, s, (const float*)partial, blocks, d, gb, d);
+                           partial, scale, row_on, blk);
+    if (gb) finish_colsum(partial, blocks, d, gb, rb, s);
 }
 
 void launch_act_bwd_bf16(const float* g, const void* act, void* dy, int64_t rows, int32_t d,
-                         float* gb, float* partial, float scale, hipStream_t s)
+                         float* gb, float* partial, float scale, hipStream_t s, const RowBlocks* rb)
 {
     if (rows <= 0) return;
     if (!act) scale = 1.f;
-    const int64_t blocks = (rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct;
+    const int64_t blocks = rb ? rb->nblocks : (rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct;
+    const int2* blk = rb ? rb->rows : nullptr;
     const bool vec = d % 4 == 0 && (reinterpret_cast<uintptr_t>(g) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(partial) & 15) == 0 &&
                      ((reinterpret_cast<uintptr_t>(act) | reinterpret_cast<uintptr_t>(dy)) & 7) == 0;
     if (vec)
         hipLaunchKernelGGL(k_act_bwd_bf16_vec, dim3((unsigned)blocks, (unsigned)((d / 4 + 63) / 64)), dim3(kBlock),
-                           0, s, g, (const uint16_t*)act, (uint16_t*)dy, rows, d, partial, scale);
+                           0, s, g, (const uint16_t*)act, (uint16_t*)dy, rows, d, partial, scale, blk);
     else
         hipLaunchKernelGGL(k_act_bwd_bf16, dim3((unsigned)blocks), dim3(kBlock), 0, s, g,
-                           (const uint16_t*)act, (uint16_t*)dy, rows, d, partial, scale);
-    if (gb)
-        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), dim3(32 * kFinishGroups), 0, s,
-                           (const float*)partial, blocks, d, gb, d);
+                           (const uint16_t*)act, (uint16_t*)dy, rows, d, partial, scale, blk);
+    if (gb) finish_colsum(partial, blocks, d, gb, rb, s);
 }
 
 void launch_dropout(void* a, int is_bf16, const int32_t* orig_of_row, int64_t rows, int32_t d,
@@ -707,7 +762,7 @@ void launch_colsum_finish(const float* partial, int64_t nblocks, int32_t d, floa
 {
     if (nblocks <= 0 || d <= 0) return;
     hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), dim3(32 * kFinishGroups), 0, s, partial, nblocks,
-                       d, out, ldp > 0 ? ldp : d);
+                       d, out, ldp > 0 ? ldp : d, (const int2*)nullptr, (float*)nullptr);
 }
 
 void launch_add_padded(float* out, const float* z, int64_t rows, int32_t d, int32_t ldz,

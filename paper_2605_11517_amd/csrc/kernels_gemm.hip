@@ -180,6 +180,7 @@ struct GemmArgs {
     int32_t accumulate;
     int64_t split_chunk;     // K per split (multiple of BK); 0 = no split
     int64_t split_stride;    // elements between the partial C of consecutive splits
+    const int2* splits;      // K range of every split (null: split_chunk apart)
     int32_t nt_1d;           // > 0: one-dimensional grid over (M tile, N tile), see tile_of_block
 };
 
@@ -222,6 +223,10 @@ __global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
     if (g.split_chunk > 0) {
         kbeg = (int64_t)blockIdx.z * g.split_chunk;
         kend0 = kbeg + g.split_chunk < kend0 ? kbeg + g.split_chunk : kend0;
+        if (g.splits) {
+            kbeg = g.splits[blockIdx.z].x;
+            kend0 = g.splits[blockIdx.z].y;
+        }
         cbase += (int64_t)blockIdx.z * g.split_stride;
     }
     // a stage is SUB consecutive k-tiles of one segment (tiles past the segment's end are zero)
@@ -344,14 +349,24 @@ __global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
 // flight) and the four sums are combined through LDS in wavefront order, so the result does
 // not depend on timing.  (One thread per group over all splits left most of the chip idle: a
 // 256 x 256 gradient is only 64 such blocks of 256 threads.)
+// With `groups` a launch holds the splits of several partitions: block row y sums those of group y,
+// the same way, and leaves the sum in group_sum at the group's place (m n floats each); k_add_groups
+// then adds the groups to c one after the other, as one launch per partition would.
 __global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict__ partial,
                                                          int32_t splits, int64_t stride,
                                                          float* __restrict__ c, int64_t ldc,
-                                                         int32_t m, int32_t n)
+                                                         int32_t m, int32_t n, const TnGroup* __restrict__ groups,
+                                                         float* __restrict__ group_sum)
 {
     constexpr int U = 8;
     __shared__ float4 sm[4][64];
     const int64_t total = (int64_t)m * n;
+    if (groups) {
+        const TnGroup q = groups[blockIdx.y];
+        partial += (int64_t)q.first * stride;
+        splits = q.count;
+        group_sum += (int64_t)q.slot * total;
+    }
     const int grp = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int64_t i = ((int64_t)blockIdx.x * 64 + grp) * 4;
     const int32_t per = (splits + 3) / 4;
@@ -385,9 +400,34 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict
     for (int e = 0; e < 4; ++e) {
         const int64_t j2 = i + e;
         if (j2 >= total) break;
-        const int64_t r = j2 / n, cc = j2 - r * n;
-        c[r * ldc + cc] += out[e];
+        if (groups) {
+            group_sum[j2] = out[e];
+        } else {
+            const int64_t r = j2 / n, cc = j2 - r * n;
+            c[r * ldc + cc] += out[e];
+        }
     }
+}
+
+// c[r, j] = (((c[r, j] + sums[0]) + sums[1]) + ...): the groups in order, eight loads in flight
+__global__ __launch_bounds__(256) void k_add_groups(const float* __restrict__ sums, int32_t ngroups, int64_t stride,
+                                                    float* __restrict__ c, int64_t ldc, int32_t m, int32_t n)
+{
+    constexpr int U = 8;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)m * n) return;
+    const int64_t r = i / n;
+    float* dst = c + r * ldc + (i - r * n);
+    float v = *dst;
+    for (int32_t g0 = 0; g0 < ngroups; g0 += U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = g0 + u < ngroups ? sums[(int64_t)(g0 + u) * stride + i] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (g0 + u < ngroups) v += x[u];
+    }
+    *dst = v;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -499,23 +539,20 @@ void launch_gemm_nt2(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64
     launch_gemm<true, true>(g, 1, s);
 }
 
-int gemm_tn_splits(int64_t kdim, int32_t m, int32_t n)
+int64_t gemm_tn_chunk(int64_t rows, int32_t m, int32_t n)
 {
     const int64_t tiles = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
-    int64_t want = (512 + tiles - 1) / tiles;           // ~2 workgroups per CU
-    int64_t most = (kdim + 16 * BK - 1) / (16 * BK);    // at least 16 k-steps per split
-    int64_t sp = want < most ? want : most;
-    return (int)(sp < 1 ? 1 : sp);
+    int64_t chunk = (rows * tiles / 2048 + BK - 1) / BK * BK;
+    chunk = chunk < 128 ? 128 : chunk;
+    return chunk > 2048 ? 2048 : chunk;
 }
 
 void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
-                    int64_t ldc, int32_t m, int32_t n, int64_t kdim, float* partial,
-                    hipStream_t s)
+                    int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t chunk, float* partial,
+                    hipStream_t s, const TnParts* parts)
 {
     if (kdim <= 0 || m <= 0 || n <= 0) return;
-    const int splits = gemm_tn_splits(kdim, m, n);
-    int64_t chunk = (kdim + splits - 1) / splits;
-    chunk = (chunk + BK - 1) / BK * BK;
+    const int splits = parts ? parts->nchunks : (int)((kdim + chunk - 1) / chunk);
     GemmArgs g{};
     g.a[0] = g.a[1] = {a, lda};
     g.b[0] = g.b[1] = {b, ldb};
@@ -523,8 +560,15 @@ void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, fl
     g.c = partial; g.ldc = n; g.m = m; g.n = n;
     g.split_chunk = chunk;
     g.split_stride = (int64_t)m * n;
+    g.splits = parts ? parts->chunks : nullptr;
     launch_gemm<false, false>(g, splits, s);
-    launch_reduce_partials(partial, splits, (int64_t)m * n, c, ldc, m, n, s);
+    if (parts) {
+        float* sums = partial + (int64_t)splits * m * n;
+        launch_reduce_groups(partial, (int64_t)m * n, m, n, *parts, sums, s);
+        launch_add_groups(sums, parts->nslots, (int64_t)m * n, c, ldc, m, n, s);
+    } else {
+        launch_reduce_partials(partial, splits, (int64_t)m * n, c, ldc, m, n, s);
+    }
 }
 
 void launch_reduce_partials(const float* partial, int splits, int64_t stride, float* c, int64_t ldc,
@@ -532,6 +576,23 @@ void launch_reduce_partials(const float* partial, int splits, int64_t stride, fl
 {
     int64_t blocks = ((int64_t)m * n + 255) / 256;
     hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)blocks), dim3(256), 0, s, partial, splits,
+                       stride, c, ldc, m, n, (const TnGroup*)nullptr, (float*)nullptr);
+}
+
+void launch_reduce_groups(const float* partial, int64_t stride, int32_t m, int32_t n, const TnParts& parts,
+                          float* sums, hipStream_t s)
+{
+    const int64_t blocks = ((int64_t)m * n + 255) / 256;
+    if (parts.ngroups <= 0) return;
+    hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)blocks, (unsigned)parts.ngroups), dim3(256), 0, s, partial, 0,
+                       stride, (float*)nullptr, 0, m, n, parts.groups, sums);
+}
+
+void launch_add_groups(const float* sums, int32_t ngroups, int64_t stride, float* c, int64_t ldc, int32_t m, int32_t n,
+                       hipStream_t s)
+{
+    if (ngroups <= 0) return;
+    hipLaunchKernelGGL(k_add_groups, dim3((unsigned)(((int64_t)m * n + 255) / 256)), dim3(256), 0, s, sums, ngroups,
                        stride, c, ldc, m, n);
 }
 

@@ -190,6 +190,7 @@ struct Args {
     const float* bias;
     int32_t relu, accumulate, out_bf16;
     int64_t split_chunk, split_stride;
+    const int2* splits;        // K range of every split (null: split_chunk apart)
     int32_t nt_1d;           // > 0: one-dimensional grid over (M tile, N tile), see tile_of_block
 };
 
@@ -229,6 +230,10 @@ __global__ __launch_bounds__(kThreads) void k_gemm_bf16(const Args g)
     if (g.split_chunk > 0) {
         kbeg = (int64_t)blockIdx.z * g.split_chunk;
         kend0 = kbeg + g.split_chunk < kend0 ? kbeg + g.split_chunk : kend0;
+        if (g.splits) {
+            kbeg = g.splits[blockIdx.z].x;
+            kend0 = g.splits[blockIdx.z].y;
+        }
         coff = (int64_t)blockIdx.z * g.split_stride;
     }
     const int64_t tiles0 = kend0 > kbeg ? (kend0 - kbeg + BK - 1) / BK : 0;
@@ -962,6 +967,7 @@ struct ArgsT {
     int64_t k;                 // rows covered, a multiple of 64
     int64_t chunk;             // rows per split, a multiple of 64
     int32_t splits;            // > 0: one-dimensional grid, see k_gemm_bf16_tn_wide
+    const int2* ranges;        // rows of every split (null: `chunk` apart)
 };
 
 __device__ inline int tn_off(int k, int mcol)          // byte offset of element (k, mcol), mcol % 4 == 0
@@ -1021,8 +1027,12 @@ __global__ __launch_bounds__(WTHREADS) void k_gemm_bf16_tn_wide(const ArgsT g)
         by = tile / mt;
     }
     const int32_t m0 = bx * WBM, n0 = by * WBN;
-    const int64_t kbeg = (int64_t)bz * g.chunk;
-    const int64_t kend = kbeg + g.chunk < g.k ? kbeg + g.chunk : g.k;
+    int64_t kbeg = (int64_t)bz * g.chunk;
+    int64_t kend = kbeg + g.chunk < g.k ? kbeg + g.chunk : g.k;
+    if (g.ranges) {
+        kbeg = g.ranges[bz].x;
+        kend = g.ranges[bz].y;
+    }
     const int nstages = kend > kbeg ? (int)((kend - kbeg) / WBK) : 0;
 
     floatx16 acc[4][2];
@@ -1076,26 +1086,6 @@ __global__ __launch_bounds__(WTHREADS) void k_gemm_bf16_tn_wide(const ArgsT g)
                 if (row < g.m) out[(int64_t)row * g.n + col] = acc[i][j][r];
             }
         }
-}
-
-bool wide_tn_ok(const void* a, int64_t lda, const void* b, int64_t ldb, int32_t m, int32_t n, int64_t kdim)
-{
-    static const bool enabled = [] {
-        const char* e = getenv("GNNMI_GEMM_WIDE");
-        return !(e && e[0] == '0');
-    }();
-    return enabled && m >= WBM && n >= WBN && m % 8 == 0 && n % 8 == 0 && kdim >= 64 * WBK && aligned16(a) &&
-           aligned16(b) && lda % 8 == 0 && ldb % 8 == 0;
-}
-
-int wide_tn_splits(int64_t kdim, int32_t m, int32_t n)
-{
-    const int64_t tiles = (int64_t)((m + WBM - 1) / WBM) * ((n + WBN - 1) / WBN);
-    int64_t want = (512 + tiles - 1) / tiles;          // two workgroups per CU over the launch
-    const int64_t most = kdim / (16 * WBK);            // at least 16 stages per split
-    int64_t sp = want < most ? want : most;
-    sp = sp > 64 ? 64 : sp;
-    return (int)(sp < 1 ? 1 : sp);
 }
 
 // dst[i] = bf16(src[i])
@@ -1152,62 +1142,101 @@ void launch_gemm_bf16_nt(const void* a, int64_t lda, const void* b, int64_t ldb,
     launch<true, true>(g, 1, s);
 }
 
-void launch_gemm_bf16_tn(const void* a, int64_t lda, const void* b, int64_t ldb, float* c,
-                         int64_t ldc, int32_t m, int32_t n, int64_t kdim, float* partial,
-                         hipStream_t s)
+bool gemm_bf16_tn_wide_ok(int64_t graph_rows, int32_t m, int32_t n, int64_t lda, int64_t ldb)
 {
-    if (kdim <= 0 || m <= 0 || n <= 0) return;
-    if (wide_tn_ok(a, lda, b, ldb, m, n, kdim)) {
-        static const bool attr_ok = hipFuncSetAttribute((const void*)k_gemm_bf16_tn_wide,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, TLDS) == hipSuccess;
-        if (attr_ok) {
-            // whole stages of 64 rows on the wide kernel, the last rows (fewer than 64) below
-            ArgsT w{};
-            w.a = (const bf16_t*)a; w.lda = lda; w.b = (const bf16_t*)b; w.ldb = ldb;
-            w.partial = partial; w.m = m; w.n = n;
-            w.k = kdim / WBK * WBK;
-            const int want = wide_tn_splits(kdim, m, n);
-            w.chunk = (w.k / WBK + want - 1) / want * WBK;
-            const int sp = (int)((w.k + w.chunk - 1) / w.chunk);
-            static const bool by_split = [] {
-                const char* e = getenv("GNNMI_GEMM_TN_XCD");
-                return !(e && e[0] == '0');
-            }();
-            const unsigned mt = (unsigned)((m + WBM - 1) / WBM), nt = (unsigned)((n + WBN - 1) / WBN);
-            if (by_split && mt * nt > 1) {
-                w.splits = sp;
-                hipLaunchKernelGGL(k_gemm_bf16_tn_wide, dim3((unsigned)((sp + 7) / 8 * 8) * mt * nt), dim3(WTHREADS),
-                                   TLDS, s, w);
-            } else {
-                w.splits = 0;
-                hipLaunchKernelGGL(k_gemm_bf16_tn_wide, dim3(mt, nt, (unsigned)sp), dim3(WTHREADS), TLDS, s, w);
-            }
-            launch_reduce_partials(partial, sp, (int64_t)m * n, c, ldc, m, n, s);
-            if (w.k == kdim) return;
-            a = (const bf16_t*)a + w.k * lda;
-            b = (const bf16_t*)b + w.k * ldb;
-            kdim -= w.k;
-        }
-    }
-    const int splits = gemm_tn_splits(kdim, m, n);
-    int64_t chunk = (kdim + splits - 1) / splits;
-    chunk = (chunk + BK - 1) / BK * BK;
-    Args g{};
-    g.a[0] = g.a[1] = (const bf16_t*)a; g.lda[0] = g.lda[1] = lda;
-    g.b[0] = g.b[1] = (const bf16_t*)b; g.ldb[0] = g.ldb[1] = ldb;
-    g.kseg[0] = (int32_t)kdim; g.kseg[1] = 0;
-    g.c = partial; g.ldc = n; g.m = m; g.n = n; g.out_bf16 = 0;
-    g.split_chunk = chunk;
-    g.split_stride = (int64_t)m * n;
-    launch<false, false>(g, splits, s);
-    launch_reduce_partials(partial, splits, (int64_t)m * n, c, ldc, m, n, s);
+    static const bool enabled = [] {
+        const char* e = getenv("GNNMI_GEMM_WIDE");
+        return !(e && e[0] == '0') && hipFuncSetAttribute((const void*)k_gemm_bf16_tn_wide,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, TLDS) == hipSuccess;
+    }();
+    return enabled && m >= WBM && n >= WBN && m % 8 == 0 && n % 8 == 0 && graph_rows >= 64 * WBK && lda % 8 == 0 &&
+           ldb % 8 == 0;
 }
 
-int64_t gemm_bf16_tn_partial_floats(int64_t kdim, int32_t m, int32_t n)
+int64_t gemm_bf16_tn_wide_chunk(int64_t graph_rows, int32_t m, int32_t n)
 {
-    const int64_t narrow = (int64_t)gemm_tn_splits(kdim, m, n) * m * n;
-    const int64_t wide = (int64_t)wide_tn_splits(kdim, m, n) * m * n;
-    return narrow > wide ? narrow : wide;
+    const int64_t tiles = (int64_t)((m + WBM - 1) / WBM) * ((n + WBN - 1) / WBN);
+    int64_t chunk = (graph_rows * tiles / 512 + WBK - 1) / WBK * WBK;
+    chunk = chunk < 8 * WBK ? 8 * WBK : chunk;
+    return chunk > 64 * WBK ? 64 * WBK : chunk;
+}
+
+void launch_gemm_bf16_tn(const void* a, int64_t lda, const void* b, int64_t ldb, float* c,
+                         int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t graph_rows, float* partial,
+                         hipStream_t s, const TnParts* wide, const TnParts* narrow)
+{
+    if (kdim <= 0 || m <= 0 || n <= 0) return;
+    const int64_t mn = (int64_t)m * n;
+    const bool use_wide = gemm_bf16_tn_wide_ok(graph_rows, m, n, lda, ldb) && aligned16(a) && aligned16(b);
+    const int64_t wide_chunk = gemm_bf16_tn_wide_chunk(graph_rows, m, n);
+    auto run_wide = [&](int64_t rows, int sp, const int2* ranges) {
+        ArgsT w{};
+        w.a = (const bf16_t*)a; w.lda = lda; w.b = (const bf16_t*)b; w.ldb = ldb;
+        w.partial = partial; w.m = m; w.n = n;
+        w.k = rows;
+        w.chunk = wide_chunk;
+        w.ranges = ranges;
+        static const bool by_split = [] {
+            const char* e = getenv("GNNMI_GEMM_TN_XCD");
+            return !(e && e[0] == '0');
+        }();
+        const unsigned mt = (unsigned)((m + WBM - 1) / WBM), nt = (unsigned)((n + WBN - 1) / WBN);
+        if (by_split && mt * nt > 1) {
+            w.splits = sp;
+            hipLaunchKernelGGL(k_gemm_bf16_tn_wide, dim3((unsigned)((sp + 7) / 8 * 8) * mt * nt), dim3(WTHREADS),
+                               TLDS, s, w);
+        } else {
+            w.splits = 0;
+            hipLaunchKernelGGL(k_gemm_bf16_tn_wide, dim3(mt, nt, (unsigned)sp), dim3(WTHREADS), TLDS, s, w);
+        }
+    };
+    auto run_narrow = [&](const void* a0, const void* b0, int64_t rows, int64_t chunk, int sp, const int2* ranges,
+                          float* out) {
+        Args g{};
+        g.a[0] = g.a[1] = (const bf16_t*)a0; g.lda[0] = g.lda[1] = lda;
+        g.b[0] = g.b[1] = (const bf16_t*)b0; g.ldb[0] = g.ldb[1] = ldb;
+        g.kseg[0] = (int32_t)rows; g.kseg[1] = 0;
+        g.c = out; g.ldc = n; g.m = m; g.n = n; g.out_bf16 = 0;
+        g.split_chunk = chunk;
+        g.split_stride = mn;
+        g.splits = ranges;
+        launch<false, false>(g, sp, s);
+    };
+    if (wide || narrow) {
+        // all partitions at once: whole stages of 64 rows of every partition on the wide kernel, the
+        // rest on the narrow one, then one sum per (partition, kernel), added in partition order
+        float* part_n = partial;
+        int slots = 0;
+        if (use_wide && wide && wide->nchunks > 0) {
+            run_wide(kdim, wide->nchunks, wide->chunks);
+            part_n = partial + wide->nchunks * mn;
+            slots += wide->ngroups;
+        }
+        float* sums = part_n;
+        if (narrow && narrow->nchunks > 0) {
+            run_narrow(a, b, kdim, gemm_tn_chunk(graph_rows, m, n), narrow->nchunks, narrow->chunks, part_n);
+            sums = part_n + narrow->nchunks * mn;
+            slots += narrow->ngroups;
+        }
+        if (use_wide && wide && wide->nchunks > 0) launch_reduce_groups(partial, mn, m, n, *wide, sums, s);
+        if (narrow && narrow->nchunks > 0) launch_reduce_groups(part_n, mn, m, n, *narrow, sums, s);
+        launch_add_groups(sums, slots, mn, c, ldc, m, n, s);
+        return;
+    }
+    if (use_wide && kdim >= WBK) {
+        const int64_t rows = kdim / WBK * WBK;
+        const int sp = (int)((rows + wide_chunk - 1) / wide_chunk);
+        run_wide(rows, sp, nullptr);
+        launch_reduce_partials(partial, sp, mn, c, ldc, m, n, s);
+        if (rows == kdim) return;
+        a = (const bf16_t*)a + rows * lda;
+        b = (const bf16_t*)b + rows * ldb;
+        kdim -= rows;
+    }
+    const int64_t chunk = gemm_tn_chunk(graph_rows, m, n);
+    const int splits = (int)((kdim + chunk - 1) / chunk);
+    run_narrow(a, b, kdim, chunk, splits, nullptr, partial);
+    launch_reduce_partials(partial, splits, mn, c, ldc, m, n, s);
 }
 
 void launch_to_bf16(const float* src, void* dst, int64_t n, hipStream_t s)

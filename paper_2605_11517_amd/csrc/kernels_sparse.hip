@@ -178,8 +178,13 @@ template <> struct Elem<uint16_t> {
     __device__ static inline void store(uint16_t* p, float v) { *p = (uint16_t)float_to_bf16(v); }
 };
 
+// Every aggregation kernel adds an entry with one fused multiply-add, written out: left to the
+// compiler, one kernel contracts `acc += w x` and another does not, and the schedules that reach a
+// row through different kernels would differ in the last bit.
+//
 // acc[v][i] += sum over entries [e_begin, e_end) of w_e * src(col_e)[(v*G + lane%G)*EPV + i]
-template <typename TIn, int G, int NV, bool VEC>
+// (FLAGS: the top two bits of a column are marks, see MergedItems)
+template <typename TIn, int G, int NV, bool VEC, bool FLAGS = false>
 __device__ inline void spmm_accumulate(const SpmmArgs& g, int64_t e_begin, int64_t e_end, int lane,
                                        float (&acc)[NV][Elem<TIn>::EPV])
 {
@@ -209,7 +214,7 @@ __device__ inline void spmm_accumulate(const SpmmArgs& g, int64_t e_begin, int64
     }
     for (int64_t e0 = e_begin; e0 < e_end; e0 += kWave) {
         const int cnt = (int)((e_end - e0) < kWave ? (e_end - e0) : kWave);
-        const int32_t cur_c = my_c;
+        const int32_t cur_c = FLAGS ? my_c & kMergedColumn : my_c;
         const float cur_w = my_w;
         if (e0 + kWave + lane < e_end) {
             my_c = g.col[e0 + kWave + lane];
@@ -243,7 +248,7 @@ __device__ inline void spmm_accumulate(const SpmmArgs& g, int64_t e_begin, int64
                         float f[EPV];
                         Elem<TIn>::unpack(x[u][v], f);
 #pragma unroll
-                        for (int i = 0; i < EPV; ++i) acc[v][i] += on ? ww[u] * f[i] : 0.f;
+                        for (int i = 0; i < EPV; ++i) acc[v][i] = on ? fmaf(ww[u], f[i], acc[v][i]) : acc[v][i];
                     }
                 }
             } else {
@@ -254,7 +259,7 @@ __device__ inline void spmm_accumulate(const SpmmArgs& g, int64_t e_begin, int64
 #pragma unroll
                         for (int i = 0; i < EPV; ++i) {
                             int c = (v * G + gl) * EPV + i;
-                            if (c < g.d && ww[u] != 0.f) acc[v][i] += ww[u] * Elem<TIn>::load(src[u] + c);
+                            if (c < g.d && ww[u] != 0.f) acc[v][i] = fmaf(ww[u], Elem<TIn>::load(src[u] + c), acc[v][i]);
                         }
             }
         }
@@ -453,7 +458,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_slots(const SpmmArgs g, int32_t
                 Elem<TIn>::unpack(x[u], f);
                 const bool on = (j0 + u) < cnt;
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) acc[i] += on ? ww[u] * f[i] : 0.f;
+                for (int i = 0; i < EPV; ++i) acc[i] = on ? fmaf(ww[u], f[i], acc[i]) : acc[i];
             }
         }
     }
@@ -605,7 +610,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_short(const SpmmArgs g, int32_t
                     float f[EPV];
                     Elem<TIn>::unpack(x[u][v], f);
 #pragma unroll
-                    for (int i = 0; i < EPV; ++i) acc[v][i] += on ? ww[u] * f[i] : 0.f;
+                    for (int i = 0; i < EPV; ++i) acc[v][i] = on ? fmaf(ww[u], f[i], acc[v][i]) : acc[v][i];
                 }
             }
         };
@@ -986,6 +991,258 @@ __global__ __launch_bounds__(kBlock) void k_spmm_long_reduce(const SpmmArgs g)
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Transposed aggregation over the whole graph (MergedItems): a row of the gradient array is summed
+// from all its destinations at once and stored once, where launches partition by partition read
+// and write it alpha times; its rows are as long as the forward operator's, so the slots and the
+// column slices of k_spmm_slots serve it as well.  Each slot of G lanes owns a row of at most one
+// segment, or one unit of a longer row; the sum runs piece by piece (acc: this piece, tot: the
+// pieces before it), the marks travelling in the top bits of the column indices.  The next chunk of
+// column indices is fetched while this one is consumed.
+// ---------------------------------------------------------------------------------------------
+struct MergedArgs {
+    MergedItems it;
+    const void* src;
+    float* out;
+    int32_t d, ld;
+};
+
+template <typename TIn, int G, int UNR, bool SELF>
+__global__ __launch_bounds__(kBlock) void k_spmm_merged(const MergedArgs g, int32_t nslices)
+{
+    constexpr int EPV = Elem<TIn>::EPV;
+    constexpr int S = kWave / G;
+    constexpr int UNROLL = G < UNR ? G : UNR;
+    const int lane = threadIdx.x % kWave;
+    const int slot = lane / G, gl = lane % G;
+    unsigned blk = blockIdx.x;
+    const int raw = (int)(blk % (unsigned)nslices) * (G * EPV) + gl * EPV;
+    const bool live = raw < g.d;
+    const int coff = live ? raw : 0;
+    blk /= (unsigned)nslices;
+    const int64_t item = ((int64_t)blk * (kBlock / kWave) + threadIdx.x / kWave) * S + slot;
+    const TIn* src = static_cast<const TIn*>(g.src);
+    int64_t e_begin = 0;
+    int32_t len = 0, row = -1;
+    bool self_first = false;
+    if (item < g.it.nunits) {
+        e_begin = g.it.unit_begin[item];
+        len = g.it.unit_len[item] & 0xFFFF;
+    } else if (item < g.it.nunits + g.it.nrows) {
+        const int32_t listed = g.it.rows[item - g.it.nunits];
+        row = listed & 0x7FFFFFFF;
+        self_first = listed < 0;
+        e_begin = g.it.rp[row];
+        len = (int32_t)(g.it.rp[row + 1] - e_begin);
+    }
+    // finished slots repeat the entries of the wavefront's longest one, see k_spmm_slots
+    int32_t maxlen = len;
+    int lead = slot;
+#pragma unroll
+    for (int m = G; m < kWave; m <<= 1) {
+        const int32_t ol = __shfl_xor(maxlen, m, kWave);
+        const int os = __shfl_xor(lead, m, kWave);
+        if (ol > maxlen || (ol == maxlen && os < lead)) { maxlen = ol; lead = os; }
+    }
+    float acc[EPV], tot[EPV], own[EPV];
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) acc[i] = tot[i] = own[i] = 0.f;
+    if (SELF && row >= 0) {
+        const float* o = g.out + (int64_t)row * g.ld + coff;
+#pragma unroll
+        for (int h = 0; h < EPV / 4; ++h) {
+            const float4 v = *reinterpret_cast<const float4*>(o + 4 * h);
+            own[4 * h] = v.x; own[4 * h + 1] = v.y; own[4 * h + 2] = v.z; own[4 * h + 3] = v.w;
+        }
+        if (self_first) {
+#pragma unroll
+            for (int i = 0; i < EPV; ++i) tot[i] = own[i];
+        }
+    }
+    int32_t nx_c = 0;
+    float nx_w = 0.f;
+    if (gl < len) {
+        nx_c = g.it.col[e_begin + gl];
+        nx_w = g.it.w[e_begin + gl];
+    }
+    for (int32_t e0 = 0; e0 < maxlen; e0 += G) {
+        const int32_t my_c = nx_c;
+        const float my_w = nx_w;
+        if (e0 + G + gl < len) {
+            nx_c = g.it.col[e_begin + e0 + G + gl];
+            nx_w = g.it.w[e_begin + e0 + G + gl];
+        }
+        const int cnt = len - e0;
+        const int lead_cnt = maxlen - e0 < G ? maxlen - e0 : G;
+        auto batch = [&](int j0) {
+            uint4 x[UNROLL];
+            float ww[UNROLL];
+            int32_t cc[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const int j = j0 + u;
+                const bool on = j < cnt;
+                const int src_lane = on ? slot * G + j : lead * G + (j < lead_cnt ? j : lead_cnt - 1);
+                cc[u] = __shfl(my_c, src_lane, kWave);
+                const float wt = __shfl(my_w, src_lane, kWave);
+                ww[u] = on ? wt : 0.f;
+                x[u] = *reinterpret_cast<const uint4*>(src + (int64_t)(cc[u] & kMergedColumn) * g.ld + coff);
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                float f[EPV];
+                Elem<TIn>::unpack(x[u], f);
+                const bool on = (j0 + u) < cnt;
+                const bool end = on && cc[u] < 0;
+                const bool self = SELF && on && (cc[u] & (int32_t)kSelfNext) != 0 && row >= 0;
+#pragma unroll
+                for (int i = 0; i < EPV; ++i) {
+                    acc[i] = on ? fmaf(ww[u], f[i], acc[i]) : acc[i];
+                    tot[i] = end ? tot[i] + acc[i] : tot[i];
+                    acc[i] = end ? 0.f : acc[i];
+                    if (SELF) tot[i] = self ? tot[i] + own[i] : tot[i];
+                }
+            }
+        };
+        if (UNR < 8) {
+#pragma unroll 1
+            for (int j0 = 0; j0 < G; j0 += UNROLL) {
+                if (j0 >= lead_cnt) break;           // uniform across the wavefront
+                batch(j0);
+            }
+        } else {
+#pragma unroll
+            for (int j0 = 0; j0 < G; j0 += UNROLL) {
+                if (j0 >= lead_cnt) break;           // uniform across the wavefront
+                batch(j0);
+            }
+        }
+    }
+    if (!live) return;
+    float* o = nullptr;
+    if (item < g.it.nunits) o = g.it.partial + item * (int64_t)g.ld + coff;
+    else if (row >= 0) o = g.out + (int64_t)row * g.ld + coff;
+    if (!o) return;
+    // (a unit that is not the last of its piece ends with its sum in acc; a row always ends a piece)
+#pragma unroll
+    for (int h = 0; h < EPV / 4; ++h)
+        *reinterpret_cast<float4*>(o + 4 * h) = make_float4(tot[4 * h] + acc[4 * h], tot[4 * h + 1] + acc[4 * h + 1],
+                                                            tot[4 * h + 2] + acc[4 * h + 2], tot[4 * h + 3] + acc[4 * h + 3]);
+}
+
+// The same for rows that are not whole 16-byte vectors: one wavefront per row or unit, a piece at a
+// time with the entry-to-slot assignment (and so the order of additions) of k_spmm_items.
+template <typename TIn, int G, int NV, bool SELF>
+__global__ __launch_bounds__(kBlock) void k_spmm_merged_any(const MergedArgs g)
+{
+    constexpr int EPV = Elem<TIn>::EPV;
+    const int lane = threadIdx.x % kWave;
+    const int64_t item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+    SpmmArgs sp{};
+    sp.col = g.it.col; sp.w = g.it.w; sp.a_rows = g.src; sp.n_a = (int64_t)1 << 40; sp.b_rows = nullptr;
+    sp.d = g.d; sp.ld = g.ld;
+    float acc[NV][EPV], tot[NV][EPV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int i = 0; i < EPV; ++i) acc[v][i] = tot[v][i] = 0.f;
+    if (item < g.it.nunits) {
+        const int64_t e0 = g.it.unit_begin[item];
+        spmm_accumulate<TIn, G, NV, false, true>(sp, e0, e0 + (g.it.unit_len[item] & 0xFFFF), lane, acc);
+        spmm_store<float, EPV, G, NV, false>(g.it.partial + item * (int64_t)g.ld, g.d, lane, 1.f, acc, false, nullptr, false);
+        return;
+    }
+    if (item >= g.it.nunits + g.it.nrows) return;
+    const int32_t listed = g.it.rows[item - g.it.nunits];
+    const int32_t row = listed & 0x7FFFFFFF;
+    const int64_t e_end = g.it.rp[row + 1];
+    float* o = g.out + (int64_t)row * g.ld;
+    auto add_self = [&] {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int i = 0; i < EPV; ++i) {
+                const int c = (v * G + lane % G) * EPV + i;
+                if (c < g.d) tot[v][i] += o[c];
+            }
+    };
+    if (SELF && listed < 0) add_self();
+    for (int64_t e = g.it.rp[row]; e < e_end;) {
+        int64_t pe = e;
+        for (;;) {                                    // the row's last entry ends a piece
+            const int32_t c = pe + lane < e_end ? g.it.col[pe + lane] : 0;
+            const unsigned long long ends = __ballot(c < 0);
+            if (ends) { pe += __ffsll((unsigned long long)ends); break; }
+            pe += kWave;
+            if (pe >= e_end) { pe = e_end; break; }
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int i = 0; i < EPV; ++i) acc[v][i] = 0.f;
+        spmm_accumulate<TIn, G, NV, false, true>(sp, e, pe, lane, acc);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int i = 0; i < EPV; ++i) tot[v][i] += acc[v][i];
+        if (SELF && (g.it.col[pe - 1] & (int32_t)kSelfNext)) add_self();
+        e = pe;
+    }
+    spmm_store<float, EPV, G, NV, false>(o, g.d, lane, 1.f, tot, false, nullptr, false);
+}
+
+// out[row,:] of the rows longer than a segment from their units' sums: one wavefront per row and
+// 256-column block, sixteen loads in flight per lane
+template <bool VEC, bool SELF>
+__global__ __launch_bounds__(kBlock) void k_spmm_merged_reduce(const MergedArgs g)
+{
+    constexpr int W = VEC ? 4 : 1, U = VEC ? 16 : 4;
+    const int lane = threadIdx.x % kWave;
+    const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+    if (i >= g.it.nlong) return;
+    const int32_t listed = g.it.long_row[i];
+    const int64_t first = g.it.long_first[i];
+    const int32_t ns = g.it.long_nunits[i];
+    float* out = g.out + (int64_t)(listed & 0x7FFFFFFF) * g.ld;
+    const int32_t cend = ((int32_t)blockIdx.y + 1) * 256 < g.d ? ((int32_t)blockIdx.y + 1) * 256 : g.d;
+    for (int32_t c = (int32_t)blockIdx.y * 256 + lane * W; c < cend; c += kWave * W) {
+        float own[W], tot[W], s[W];
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+            own[e] = SELF ? out[c + e] : 0.f;
+            tot[e] = SELF && listed < 0 ? own[e] : 0.f;
+            s[e] = 0.f;
+        }
+        for (int32_t t0 = 0; t0 < ns; t0 += U) {
+            float x[U][W];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t t = t0 + u < ns ? t0 + u : ns - 1;
+                const float* q = g.it.partial + (first + t) * (int64_t)g.ld + c;
+                if constexpr (VEC) {
+                    const float4 v = *reinterpret_cast<const float4*>(q);
+                    x[u][0] = v.x; x[u][1] = v.y; x[u][2] = v.z; x[u][3] = v.w;
+                } else {
+                    x[u][0] = *q;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (t0 + u >= ns) break;
+                const uint32_t fl = (uint32_t)g.it.unit_len[first + t0 + u];
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    s[e] += x[u][e];
+                    if (fl & kPieceEnd) { tot[e] += s[e]; s[e] = 0.f; }
+                    if (SELF && (fl & kSelfNext)) tot[e] += own[e];
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < W; ++e) out[c + e] = tot[e];
+    }
+}
+
 // dst[map(i),:] += src[i,:]
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_scatter_add(const float* __restrict__ src, int64_t nrows,
@@ -1166,6 +1423,21 @@ void spmm_typed(const int64_t* rp, const int32_t* col, const float* w, const flo
         else hipLaunchKernelGGL((k_spmm_slots<TIn, TOut, 32>), grid1, dim3(kBlock), 0, s, g, 1);
         return;
     }
+    if (vec && nvec > 256 && items.rows_sorted && (sc.n_own < 0 || sizeof(TOut) == 4) && items.nsegs + items.nshort > 0) {
+        // rows wider than 256 vectors: column slices of 256 bytes, one slot per row, so that every
+        // column is summed in the order of the entries (column blocks of k_spmm_items would give the
+        // last, narrow block another order)
+        const int ns = (nvec + 15) / 16;
+        const int64_t blocks = (items.nsegs + items.nshort + (int64_t)wpb * 4 - 1) / ((int64_t)wpb * 4);
+        SpmmArgs g;
+        g.rp = rp; g.col = col; g.w = w; g.rowscale = rowscale;
+        g.a_rows = a_rows; g.n_a = n_a; g.b_rows = b_rows; g.out = out; g.d = d; g.ld = ld;
+        g.it = items; g.partial = partial;
+        g.map_n_own = sc.n_own; g.map_base = sc.base_row; g.map_idx = sc.idx; g.map_first = sc.first;
+        g.bias = sc.bias; g.relu = sc.relu;
+        hipLaunchKernelGGL((k_spmm_slots<TIn, TOut, 16>), dim3((unsigned)(blocks * ns)), dim3(kBlock), 0, s, g, ns);
+        return;
+    }
     const int64_t nitems = items.nsegs + items.nranges;
     const dim3 grid((unsigned)((nitems + wpb - 1) / wpb));
     const dim3 block(kBlock);
@@ -1278,6 +1550,89 @@ bool launch_spmm_heads(const int64_t* rp, const int32_t* col, const float* w, in
     else if (few2) hipLaunchKernelGGL((k_spmm_short<float, float, 32, 4, 1, false>), grid, dim3(kBlock), 0, s, g, nh);
     else hipLaunchKernelGGL((k_spmm_slots<float, float, 32>), grid, dim3(kBlock), 0, s, g, nh);
     return true;
+}
+
+namespace {
+template <typename TIn>
+void spmm_merged_typed(const MergedArgs& g0, int self, hipStream_t s)
+{
+    constexpr int EPV = Elem<TIn>::EPV;
+    MergedArgs g = g0;
+    const int64_t n_items = g.it.nunits + g.it.nrows;
+    const int wpb = kBlock / kWave;
+    const int32_t d = g.d;
+    const int nvec = (d + EPV - 1) / EPV;
+    if (d % EPV == 0) {
+        // slots of 4 to 32 vectors; wider rows in column slices of 256 bytes (see spmm_typed)
+        const int G = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 16;
+        const int ns = (nvec + G - 1) / G;
+        const int S = kWave / G;
+        const int64_t blocks = (n_items + (int64_t)wpb * S - 1) / ((int64_t)wpb * S);
+        const dim3 grid((unsigned)(blocks * ns));
+        const bool few = g.it.avg_len < short_rows_max();
+#define GNN_MERGED(G, U)                                                                                          \
+    do {                                                                                                          \
+        if (self) hipLaunchKernelGGL((k_spmm_merged<TIn, G, U, true>), grid, dim3(kBlock), 0, s, g, ns);          \
+        else hipLaunchKernelGGL((k_spmm_merged<TIn, G, U, false>), grid, dim3(kBlock), 0, s, g, ns);              \
+    } while (0)
+        if (G == 4) GNN_MERGED(4, 4);
+        else if (G == 8 && few) GNN_MERGED(8, 4);
+        else if (G == 8) GNN_MERGED(8, 8);
+        else if (G == 16 && few) GNN_MERGED(16, 4);
+        else if (G == 16) GNN_MERGED(16, 8);
+        else if (few) GNN_MERGED(32, 4);
+        else GNN_MERGED(32, 8);
+#undef GNN_MERGED
+        return;
+    }
+    // (column blocks as in spmm_typed)
+    constexpr int32_t kColBlock = 256 * EPV;
+    const dim3 grid((unsigned)((n_items + wpb - 1) / wpb));
+    for (int32_t c0 = 0; c0 < d; c0 += kColBlock) {
+        g = g0;
+        g.d = d - c0 < kColBlock ? d - c0 : kColBlock;
+        g.src = static_cast<const TIn*>(g0.src) + c0;
+        g.out = g0.out + c0;
+        g.it.partial = g0.it.partial + c0;
+        const int nv = (g.d + EPV - 1) / EPV;
+#define GNN_MERGED(G, NV)                                                                                         \
+    do {                                                                                                          \
+        if (self) hipLaunchKernelGGL((k_spmm_merged_any<TIn, G, NV, true>), grid, dim3(kBlock), 0, s, g);         \
+        else hipLaunchKernelGGL((k_spmm_merged_any<TIn, G, NV, false>), grid, dim3(kBlock), 0, s, g);             \
+    } while (0)
+        if (nv <= 8) GNN_MERGED(8, 1);
+        else if (nv <= 16) GNN_MERGED(16, 1);
+        else if (nv <= 32) GNN_MERGED(32, 1);
+        else if (nv <= 64) GNN_MERGED(64, 1);
+        else if (nv <= 128) GNN_MERGED(64, 2);
+        else GNN_MERGED(64, 4);
+#undef GNN_MERGED
+    }
+}
+}  // namespace
+
+void launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
+                        int self, hipStream_t s)
+{
+    if (d <= 0 || it.nunits + it.nrows <= 0) return;
+    MergedArgs g{it, src, out, d, d};
+    if (in_bf16) spmm_merged_typed<uint16_t>(g, self, s);
+    else spmm_merged_typed<float>(g, self, s);
+}
+
+void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s)
+{
+    if (it.nlong <= 0 || d <= 0) return;
+    MergedArgs g{it, nullptr, out, d, d};
+    const int wpb = kBlock / kWave;
+    const dim3 grid((unsigned)((it.nlong + wpb - 1) / wpb), (unsigned)((d + 255) / 256));
+    if (d % 4 == 0) {
+        if (self) hipLaunchKernelGGL((k_spmm_merged_reduce<true, true>), grid, dim3(kBlock), 0, s, g);
+        else hipLaunchKernelGGL((k_spmm_merged_reduce<true, false>), grid, dim3(kBlock), 0, s, g);
+    } else {
+        if (self) hipLaunchKernelGGL((k_spmm_merged_reduce<false, true>), grid, dim3(kBlock), 0, s, g);
+        else hipLaunchKernelGGL((k_spmm_merged_reduce<false, false>), grid, dim3(kBlock), 0, s, g);
+    }
 }
 
 bool spmm_gemm_fused_init();
