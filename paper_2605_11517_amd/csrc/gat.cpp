@@ -59,7 +59,7 @@ GatView view(gnn_ctx* c, int32_t layer, int32_t p, int32_t h)
     v.r0 = M.off[(size_t)p];
     v.np = M.off[(size_t)p + 1] - v.r0;
     v.nb = M.boff[(size_t)p + 1] - M.boff[(size_t)p];
-    v.e0 = M.rp[(size_t)v.r0];
+    v.e0 = M.rp.empty() ? 0 : M.rp[(size_t)v.r0];     // (whole graph: no row pointers here)
     v.din = c->dims[(size_t)layer - 1];
     v.dout = c->dims[(size_t)layer];
     v.nh = c->nheads(layer);
@@ -113,7 +113,8 @@ GatRowsHost rows_of(gnn_ctx* c, const GatView& v, int32_t p)
     h.hs = v.hs;
     h.items = plan_items(c->M.plan_fwd, c->D.fwd, p);
     // entries per row: the aggregation launchers pick their short-row kernels by it
-    h.items.avg_len = (float)(c->M.rp[(size_t)(v.r0 + v.np)] - v.e0) / (float)std::max<int64_t>(1, v.np);
+    const int64_t entries = c->M.rp.empty() ? c->M.stats.nnz : c->M.rp[(size_t)(v.r0 + v.np)] - v.e0;
+    h.items.avg_len = (float)entries / (float)std::max<int64_t>(1, v.np);
     return h;
 }
 
@@ -230,8 +231,10 @@ void gat_bwd_begin(gnn_ctx* c, int32_t layer, hipStream_t s)
     const int64_t n = c->M.n;
     const int64_t nh = c->nheads(layer);
     Timed t(c, s, GNN_K_OTHER);
-    launch_fill_zero(c->ghbuf, n * (int64_t)c->hrow(layer) * 4, s);
-    launch_fill_zero(c->scratch + c->ws.gssrc, n * nh * 4, s);
+    if (!c->merged_transpose()) {     // (over the whole graph both are stored, not added to)
+        launch_fill_zero(c->ghbuf, n * (int64_t)c->hrow(layer) * 4, s);
+        launch_fill_zero(c->scratch + c->ws.gssrc, n * nh * 4, s);
+    }
     launch_fill_zero(c->scratch + c->ws.gsdst, n * nh * 4, s);
     // grad A^{l-1} needs no initialisation: each of its rows is written once, by grad H_p W^T
 }
@@ -252,16 +255,20 @@ void gat_layer_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
             // (dropout followed the activation: its dropped elements are the zeros of the stored
             // rows, the others carry the factor 1 / (1 - p))
             launch_act_bwd(g_own, (const float*)c->act[(size_t)layer - 1] + v0.r0 * v0.dout, dYbuf, v0.np, v0.dout, gb,
-                           colpart, c->dropout_p > 0.f ? 1.f / (1.f - c->dropout_p) : 1.f, s);
+                           colpart, c->dropout_p > 0.f ? 1.f / (1.f - c->dropout_p) : 1.f, s, nullptr, row_blocks(c));
             dY = dYbuf;
         } else {
-            launch_act_bwd(g_own, nullptr, nullptr, v0.np, v0.dout, gb, colpart, 1.f, s);
+            launch_act_bwd(g_own, nullptr, nullptr, v0.np, v0.dout, gb, colpart, 1.f, s, nullptr, row_blocks(c));
         }
     }
-    const int64_t t0 = M.toff[(size_t)p];
-    SpmmItems titems = plan_items(M.plan_bwd, c->D.bwd, p);
-    titems.avg_len = (float)(M.trp[(size_t)M.toff[(size_t)p + 1]] - M.trp[(size_t)t0]) /
-                     (float)std::max<int64_t>(1, v0.np + v0.nb);
+    const bool merged = c->merged_transpose();
+    const int64_t t0 = merged ? 0 : M.toff[(size_t)p];
+    SpmmItems titems;
+    if (!merged) {
+        titems = plan_items(M.plan_bwd, c->D.bwd, p);
+        titems.avg_len = (float)(M.trp[(size_t)M.toff[(size_t)p + 1]] - M.trp[(size_t)t0]) /
+                         (float)std::max<int64_t>(1, v0.np + v0.nb);
+    }
     const int32_t* bnd = c->D.bnd + M.boff[(size_t)p];
     float* segpart = (float*)(c->scratch + c->ws.segpart);
     const GatRowsHost rows = rows_of(c, v0, p);
@@ -299,8 +306,37 @@ void gat_layer_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
     {
         Timed t(c, s, GNN_K_OTHER);     // every head
         launch_gat_bwd_scalars(rows, v0.att, v0.dal, v0.pair, v0.gsdst + v0.r0 * nh, segpart, s);
-        launch_gat_transposed(c->D.trp + t0, c->D.tperm, v0.e0, v0.np, v0.r0, bnd, titems, v0.pair, v0.twatt,
-                              v0.gssrc, nh, v0.hs, segpart, s);
+        if (!merged)
+            launch_gat_transposed(c->D.trp + t0, c->D.tperm, v0.e0, v0.np, v0.r0, bnd, titems, v0.pair, v0.twatt,
+                                  v0.gssrc, nh, v0.hs, segpart, s);
+        else
+            launch_gat_merged(merged_items(c->D.merged), v0.pair, v0.twatt, v0.gssrc, nh, v0.hs, c->D.merged.partial, s);
+    }
+    if (merged) {
+        // every partition at once (see MergedItems): rows of grad H are stored, with all heads in one
+        // launch where they lie side by side and suit the slots
+        MergedItems it = merged_items(c->D.merged);
+        bool all = false;
+        if (v0.side) {
+            it.w = v0.twatt;
+            Timed t(c, s, GNN_K_SPMM_T);
+            all = launch_spmm_merged(it, dY, 0, v0.gH, v0.ldh, 0, s, v0.ldh, nh, v0.hs);
+        }
+        if (all) {
+            Timed t(c, s, GNN_K_SPMM_REDUCE);
+            launch_spmm_merged_reduce(it, v0.gH, v0.ldh, 0, s, v0.ldh);
+        }
+        for (int32_t h = 0; h < nh && !all; ++h) {
+            const GatView v = view(c, layer, p, h);
+            it.w = v.twatt;
+            {
+                Timed t(c, s, GNN_K_SPMM_T);
+                launch_spmm_merged(it, dy_of(v, h), 0, v.gH, v.fp, 0, s, v.ldh);
+            }
+            Timed t(c, s, GNN_K_SPMM_REDUCE);
+            launch_spmm_merged_reduce(it, v.gH, v.fp, 0, s, v.ldh);
+        }
+        return;
     }
     SpmmScatter sc;
     sc.n_own = v0.np;
@@ -340,14 +376,16 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
     const GatView v0 = view(c, layer, p, 0);
     const float* in_own = (const float*)c->layer_input(layer, v0.r0);
     float* gprev = layer >= 2 ? c->gact[(size_t)layer - 2] + v0.r0 * v0.din : nullptr;
+    const RowBlocks* rb = row_blocks(c);
+    const int64_t blocks = rb ? rb->nblocks : (v0.np + 255) / 256;
     if (nh == 1 || v0.side) {
         // whole rows: one rank-one update, one weight gradient, one input gradient
         float* gHp = v0.gH + v0.own();
         {
             Timed t(c, s, GNN_K_OTHER);
             launch_gat_rank1(gHp, v0.H + v0.own(), v0.ldh, v0.dout, v0.np, v0.gssrc + v0.r0 * nh, v0.gsdst + v0.r0 * nh,
-                             nh, v0.f, v0.a_src, v0.a_dst, part, s);
-            launch_colsum_finish(part, (v0.np + 255) / 256, 2 * v0.dout, ga, s);
+                             nh, v0.f, v0.a_src, v0.a_dst, part, s, rb);
+            launch_colsum_finish(part, blocks, 2 * v0.dout, ga, s, 0, rb, part + blocks * 2 * v0.dout);
         }
         {
             Timed t(c, s, GNN_K_GEMM_DW);
@@ -365,9 +403,10 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
         {
             Timed t(c, s, GNN_K_OTHER);
             launch_gat_rank1(gHp, v.H + v.own(), v.ldh, v.f, v.np, v.gssrc + v.r0 * nh, v.gsdst + v.r0 * nh, nh, v.f,
-                             v.a_src, v.a_dst, part, s);
-            launch_colsum_finish(part, (v.np + 255) / 256, v.f, ga + (int64_t)h * v.f, s, 2 * v.f);
-            launch_colsum_finish(part + v.f, (v.np + 255) / 256, v.f, ga + v.dout + (int64_t)h * v.f, s, 2 * v.f);
+                             v.a_src, v.a_dst, part, s, rb);
+            float* sums = part + blocks * 2 * v.f;
+            launch_colsum_finish(part, blocks, v.f, ga + (int64_t)h * v.f, s, 2 * v.f, rb, sums);
+            launch_colsum_finish(part + v.f, blocks, v.f, ga + v.dout + (int64_t)h * v.f, s, 2 * v.f, rb, sums);
         }
         Timed t(c, s, GNN_K_GEMM_DW);
         weight_grad(c, in_own, v.din, gHp, v.ldh, gW + (int64_t)h * v.f, v.dout, v.din, v.f, v.np, splitk, s);

@@ -362,7 +362,7 @@ void compute_workspace(gnn_ctx* c)
     w.partial2 = c->is_whole ? w.partial : take(part);
     // (whole graph: a part of a block and a sum of its own for every partition)
     w.colpart = take(std::max(act_bwd_partial_floats(max_np, (int32_t)dout),
-                              gat_rank1_partial_floats(max_np, (int32_t)dout)) + 2 * (int64_t)c->parts_k * dout);
+                              gat_rank1_partial_floats(max_np, (int32_t)dout)) + 4 * (int64_t)c->parts_k * dout);
     w.losspart = take(loss_partial_floats(M.n, std::max(M.k, c->parts_k)));
     w.segpart = take(std::max(M.plan_fwd.max_segs, M.plan_bwd.max_segs) * din);
     if (c->bf16()) {
@@ -494,8 +494,6 @@ void apply_dropout(gnn_ctx* c, int32_t layer, int64_t r0, int64_t rows, void* ou
     launch_dropout(out_own, is_bf16, c->D.order + r0, rows, c->dims[(size_t)layer], key, threshold,
                    1.f / (1.f - c->dropout_p), s);
 }
-
-static const RowBlocks* row_blocks(const gnn_ctx* c) { return c->is_whole ? &c->tables.rb : nullptr; }
 
 void weight_grad(gnn_ctx* c, const void* a, int64_t lda, const void* b, int64_t ldb, float* out, int64_t ldc, int32_t m,
                  int32_t n, int64_t rows, float* partial, hipStream_t s)

@@ -51,6 +51,7 @@ struct DevMeta {
         int64_t* rp = nullptr;
         int32_t* col = nullptr;
         float* w = nullptr;
+        int32_t* perm = nullptr;    // attention: forward position of every entry, in place of w
         int32_t* rows = nullptr;
         int64_t* unit_begin = nullptr;
         int32_t* unit_len = nullptr;
@@ -358,6 +359,8 @@ void xf_aggregate_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, 
 void xf_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, const float* g_own,
                       const char* act_own, float* gprev_own, hipStream_t s);
 
+inline const RowBlocks* row_blocks(const gnn_ctx* c) { return c->is_whole ? &c->tables.rb : nullptr; }
+MergedItems merged_items(const DevMeta::Merged& m);
 void compute_workspace(gnn_ctx* c);
 gnn_status epoch_resident(gnn_ctx* c, void* stream, float* loss_out);
 // c += A^T B over `rows` rows of one partition (or, in the whole-graph schedule, of all of them,

@@ -192,6 +192,7 @@ struct MergedItems {
     const int64_t* rp = nullptr;
     const int32_t* col = nullptr;     // destination row | flags
     const float* w = nullptr;
+    const int32_t* perm = nullptr;    // attention: position of the entry in the forward operator
     const int32_t* rows = nullptr;    // rows of at most `segment` entries, longest first; top bit: the
     int64_t nrows = 0;                // self term comes before every piece
     // longer rows: units (pieces, or segments of a piece) summed on their own and combined per row
@@ -210,9 +211,12 @@ constexpr int32_t kMergedColumn = 0x3FFFFFFF;
 // out[u,:] = sum over the entries of row u of w src[col,:] for every row u (fp32 sums; rows d elements
 // apart on both sides).  self: out holds the self term when the kernel starts, which is added
 // where the flags say.
-void launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
-                        int self, hipStream_t s);
-void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s);
+// ld (0: d): rows of src, out and partial start ld elements apart.  heads > 1: column slices of
+// d / heads columns each, slice j with the entry weights w + j wss (see launch_spmm_heads; false,
+// nothing launched, when the slice width does not suit the slots).
+bool launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
+                        int self, hipStream_t s, int32_t ld = 0, int32_t heads = 1, int64_t wss = 0);
+void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s, int32_t ld = 0);
 
 // Building it on the device (kernels_merge.hip) from the per-partition transposes.
 // cnt[u] += entries of every row of every T_p^T that belongs to vertex u
@@ -220,9 +224,10 @@ void launch_merge_count(int64_t nrows, int32_t k, const int64_t* toff, const int
                         const int32_t* bnd, const int64_t* trp, int32_t* cnt, hipStream_t s);
 // appends partition p's piece of every row at cursor[row]; self_first (may be null): marks for
 // GraphSAGE's self term
+// tw -> w, or (attention) tperm + e0 -> perm
 void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, const int64_t* trp, const int32_t* tcol,
-                       const float* tw, const int64_t* rp, int64_t* cursor, int32_t* col, float* w,
-                       uint8_t* self_first, hipStream_t s);
+                       const float* tw, const int32_t* tperm, int64_t e0, const int64_t* rp, int64_t* cursor, int32_t* col,
+                       float* w, int32_t* perm, uint8_t* self_first, hipStream_t s);
 // the operator restricted to destinations with mask != 0: entries kept per row, then the entries
 void launch_merge_mask_count(int64_t n, const int64_t* rp, const int32_t* col, const uint8_t* mask, int32_t* cnt,
                              hipStream_t s);
@@ -448,10 +453,17 @@ void launch_gat_transposed(const int64_t* trp, const int32_t* tperm, int64_t e0,
 int64_t gat_rank1_partial_floats(int64_t rows, int32_t f);
 void launch_gat_rank1(float* gH, const float* H, int32_t ld, int32_t f, int64_t rows, const float* gs_src,
                       const float* gs_dst, int32_t nh, int32_t fh, const float* a_src, const float* a_dst,
-                      float* partial, hipStream_t s);
+                      float* partial, hipStream_t s, const RowBlocks* rb = nullptr);
+// transposed entries over the whole graph, every head: tw_att[h hs + e] = attention weight of entry
+// it.perm[e]; gs_src[row nh + h] = sum over the row of the score gradients; stat: nh it.nunits floats
+struct MergedItems;
+void launch_gat_merged(const MergedItems& it, const float* pair, float* tw_att, float* gs_src, int32_t nh, int64_t hs,
+                       float* stat, hipStream_t s);
 // out[c] += sum over b < nblocks of partial[b * ldp + c] for c < d (ldp = 0: rows of d floats)
+// rb: the partial rows are those of all partitions, summed partition by partition; sums: room for
+// ngroups d floats
 void launch_colsum_finish(const float* partial, int64_t nblocks, int32_t d, float* out, hipStream_t s,
-                          int32_t ldp = 0);
+                          int32_t ldp = 0, const RowBlocks* rb = nullptr, float* sums = nullptr);
 
 // Transform-first layers: out = (accumulate ? out : 0) + z[:, :d] (+ bias), optional relu, with
 // z's row stride ldz >= d and out's row stride ldo (0: d); and a row copy into a wider,

@@ -688,22 +688,6 @@ int64_t act_bwd_partial_floats(int64_t rows, int32_t d)
     return ((rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct) * (int64_t)d;
 }
 
-// gb += column sums of the partial rows: those of one partition, or partition by partition
-static void finish_colsum(const float* partial, int64_t nblocks, int32_t d, float* gb, const RowBlocks* rb,
-                          hipStream_t s)
-{
-    const dim3 block(32 * kFinishGroups);
-    if (rb) {
-        float* sums = const_cast<float*>(partial) + nblocks * d;
-        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32), (unsigned)rb->ngroups), block, 0, s, partial,
-                           nblocks, d, gb, d, rb->groups, sums);
-        launch_add_groups(sums, rb->ngroups, d, gb, d, 1, d, s);
-    } else {
-        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), block, 0, s, partial, nblocks, d, gb, d,
-                           (const int2*)nullptr, (float*)nullptr);
-    }
-}
-
 void launch_act_bwd(const float* g, const float* act, float* dy, int64_t rows, int32_t d,
                     float* gb, float* partial, float scale, hipStream_t s, const uint8_t* row_on, const RowBlocks* rb)
 {
@@ -722,7 +706,7 @@ void launch_act_bwd(const float* g, const float* act, float* dy, int64_t rows, i
     else
         hipLaunchKernelGGL(k_act_bwd, dim3((unsigned)blocks), dim3(kBlock), 0, s, g, act, dy, rows, d,
                            partial, scale, row_on, blk);
-    if (gb) finish_colsum(partial, blocks, d, gb, rb, s);
+    if (gb) launch_colsum_finish(partial, blocks, d, gb, s, d, rb, partial + blocks * d);
 }
 
 void launch_act_bwd_bf16(const float* g, const void* act, void* dy, int64_t rows, int32_t d,
@@ -741,7 +725,7 @@ void launch_act_bwd_bf16(const float* g, const void* act, void* dy, int64_t rows
     else
         hipLaunchKernelGGL(k_act_bwd_bf16, dim3((unsigned)blocks), dim3(kBlock), 0, s, g,
                            (const uint16_t*)act, (uint16_t*)dy, rows, d, partial, scale, blk);
-    if (gb) finish_colsum(partial, blocks, d, gb, rb, s);
+    if (gb) launch_colsum_finish(partial, blocks, d, gb, s, d, rb, partial + blocks * d);
 }
 
 void launch_dropout(void* a, int is_bf16, const int32_t* orig_of_row, int64_t rows, int32_t d,
@@ -758,11 +742,20 @@ void launch_dropout(void* a, int is_bf16, const int32_t* orig_of_row, int64_t ro
                            orig_of_row, rows, d, (unsigned long long)key, threshold, scale);
 }
 
-void launch_colsum_finish(const float* partial, int64_t nblocks, int32_t d, float* out, hipStream_t s, int32_t ldp)
+void launch_colsum_finish(const float* partial, int64_t nblocks, int32_t d, float* out, hipStream_t s, int32_t ldp,
+                          const RowBlocks* rb, float* sums)
 {
     if (nblocks <= 0 || d <= 0) return;
-    hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), dim3(32 * kFinishGroups), 0, s, partial, nblocks,
-                       d, out, ldp > 0 ? ldp : d, (const int2*)nullptr, (float*)nullptr);
+    const dim3 block(32 * kFinishGroups);
+    ldp = ldp > 0 ? ldp : d;
+    if (rb) {
+        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32), (unsigned)rb->ngroups), block, 0, s, partial,
+                           nblocks, d, out, ldp, rb->groups, sums);
+        launch_add_groups(sums, rb->ngroups, d, out, d, 1, d, s);
+    } else {
+        hipLaunchKernelGGL(k_colsum_finish, dim3((unsigned)((d + 31) / 32)), block, 0, s, partial, nblocks, d, out, ldp,
+                           (const int2*)nullptr, (float*)nullptr);
+    }
 }
 
 void launch_add_padded(float* out, const float* z, int64_t rows, int32_t d, int32_t ldz,

@@ -697,39 +697,71 @@ struct GatTRows {
     int64_t nranges;
     int32_t segment;
 };
+// Sum of the score gradients of four heads h0 .. h0 + 3 (those below h0 + nhb) over the transposed
+// entries [eb, ee), by a group of 16 lanes: entries 16 apart per lane, then a shuffle tree.  Every
+// pass over transposed rows sums a row, a segment or a piece this way.  The attention weights of
+// those entries are written to tw_att on the way.  EVEN: nh is even, two heads' pairs are read as
+// one 16-byte vector.
+constexpr int kTHeads = 4;
+template <bool EVEN>
+__device__ inline void trow_sum(const float* __restrict__ pair, const int32_t* __restrict__ tperm, int64_t eb, int64_t ee,
+                                int gl, int32_t nh, int32_t h0, int nhb, float* __restrict__ tw_att, int64_t hs,
+                                int64_t e0, float (&sum)[kTHeads])
+{
+    constexpr int GW = kGroup, HB = kTHeads;
+#pragma unroll
+    for (int b = 0; b < HB; ++b) sum[b] = 0.f;
+    for (int64_t e = eb + gl; e < ee; e += GW) {
+        const float* q = pair + ((int64_t)tperm[e] * nh + h0) * 2;
+        float av[HB], dv[HB];
+        if (EVEN) {
+#pragma unroll
+            for (int b = 0; b < HB; b += 2) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (b < nhb) v = *reinterpret_cast<const float4*>(q + 2 * b);
+                av[b] = v.x; dv[b] = v.y; av[b + 1] = v.z; dv[b + 1] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < HB; ++b) {
+                float2 v = make_float2(0.f, 0.f);
+                if (b < nhb) v = *reinterpret_cast<const float2*>(q + 2 * b);
+                av[b] = v.x; dv[b] = v.y;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < HB; ++b)
+            if (b < nhb) {
+                tw_att[(h0 + b) * hs + e - e0] = av[b];
+                sum[b] += dv[b];
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < HB; ++b)
+#pragma unroll
+        for (int m = 1; m < GW; m <<= 1) sum[b] += __shfl_xor(sum[b], m, kWave);
+}
+
 // Long transposed rows (a hub as a source: up to 10^5 destinations in one partition) are cut
-// into the aggregation's segments like the long forward rows: one wavefront per segment and all
-// heads, then one wavefront per row adds the segments' sums in segment order.  (A workgroup per
-// row walked a hub's entries in a hundred dependent steps: 245 us per launch, whatever the heads.)
+// into the aggregation's segments like the long forward rows: 16 lanes per segment, then one
+// wavefront per row adds the segments' sums.  (A workgroup per row walked a hub's entries in a
+// hundred dependent steps: 245 us per launch, whatever the heads.)
+template <bool EVEN>
 __global__ __launch_bounds__(kBlock) void k_gat_tsegs(const GatTRows g, const GatSegs q,
                                                       const float* __restrict__ pair, float* __restrict__ tw_att,
                                                       float* __restrict__ stat)
 {
-    const int t = threadIdx.x % kWave;
-    const int64_t sgi = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    const int gl = threadIdx.x % kGroup;
+    const int64_t sgi = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
     if (sgi >= q.nsegs) return;
     const int64_t eb = q.seg_begin[sgi], ee = eb + q.seg_len[sgi];
-    int32_t fe[kPerLane];
+    for (int32_t h0 = 0; h0 < g.nh; h0 += kTHeads) {
+        const int nhb = g.nh - h0 < kTHeads ? g.nh - h0 : kTHeads;
+        float sum[kTHeads];
+        trow_sum<EVEN>(pair, g.tperm, eb, ee, gl, g.nh, h0, nhb, tw_att, g.hs, g.e0, sum);
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-        const int64_t e = eb + t + (int64_t)i * kWave;
-        fe[i] = e < ee ? g.tperm[e] : -1;
-    }
-    for (int32_t h = 0; h < g.nh; ++h) {
-        float2 v[kPerLane];
-#pragma unroll
-        for (int i = 0; i < kPerLane; ++i)
-            v[i] = fe[i] >= 0 ? *reinterpret_cast<const float2*>(pair + ((int64_t)fe[i] * g.nh + h) * 2)
-                              : make_float2(0.f, 0.f);
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < kPerLane; ++i) {
-            const int64_t e = eb + t + (int64_t)i * kWave;
-            if (e < ee) tw_att[h * g.hs + e - g.e0] = v[i].x;
-            sum += v[i].y;
-        }
-        sum = wave_sum(sum);
-        if (t == 0) stat[(int64_t)h * q.nsegs + sgi] = sum;
+        for (int b = 0; b < kTHeads; ++b)
+            if (gl == 0 && b < nhb) stat[(int64_t)(h0 + b) * q.nsegs + sgi] = sum[b];
     }
 }
 __global__ __launch_bounds__(kBlock) void k_gat_tcombine(const GatTRows g, const GatSegs q,
@@ -747,69 +779,112 @@ __global__ __launch_bounds__(kBlock) void k_gat_tcombine(const GatTRows g, const
         if (t == 0) gs_src[r * g.nh + h] += v;
     }
 }
-// EVEN: nh is even, two heads' pairs are read as one 16-byte vector
 template <bool EVEN>
 __global__ __launch_bounds__(kBlock) void k_gat_trows(const GatTRows g, const float* __restrict__ pair,
                                                       float* __restrict__ tw_att, float* __restrict__ gs_src)
 {
-    {
-        // transposed rows are short (a source feeds about ten destinations of a partition): a
-        // group of 16 lanes takes a row, four rows of the item at a time, four heads at a time
-        constexpr int GW = 16, HB = 4;
-        const int lane = threadIdx.x % kWave, gl = lane % GW, grp = lane / GW;
-        const int64_t item = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-        if (item >= g.nranges) return;
-        const int32_t r1 = g.range_rows[item + 1];
-        // (every lane of the wavefront runs the same number of row steps: the shuffles below
-        // need all 64 lanes; lanes without a row take an empty one)
-        for (int32_t i0 = g.range_rows[item]; i0 < r1; i0 += kWave / GW) {
-            const int32_t i = i0 + grp;
-            int64_t eb = 0, ee = 0;
-            if (i < r1) {
-                eb = g.trp[i];
-                ee = g.trp[i + 1];
-                if (ee - eb > g.segment) ee = eb;      // long rows: the other kernel
-            }
-            for (int32_t h0 = 0; h0 < g.nh; h0 += HB) {
-                const int nhb = g.nh - h0 < HB ? g.nh - h0 : HB;
-                float sum[HB] = {0.f, 0.f, 0.f, 0.f};
-                for (int64_t e = eb + gl; e < ee; e += GW) {
-                    const float* q = pair + ((int64_t)g.tperm[e] * g.nh + h0) * 2;
-                    float av[HB], dv[HB];
-                    if (EVEN) {
+    // transposed rows are short (a source feeds about ten destinations of a partition): a
+    // group of 16 lanes takes a row, four rows of the item at a time, four heads at a time
+    const int lane = threadIdx.x % kWave, gl = lane % kGroup, grp = lane / kGroup;
+    const int64_t item = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    if (item >= g.nranges) return;
+    const int32_t r1 = g.range_rows[item + 1];
+    for (int32_t i = g.range_rows[item] + grp; i < r1; i += kWave / kGroup) {
+        const int64_t eb = g.trp[i], ee = g.trp[i + 1];
+        if (ee <= eb || ee - eb > g.segment) continue;      // long rows: the other kernels
+        const int64_t r = i < g.n_own ? g.base_row + i : (int64_t)g.bnd[i - g.n_own];
+        for (int32_t h0 = 0; h0 < g.nh; h0 += kTHeads) {
+            const int nhb = g.nh - h0 < kTHeads ? g.nh - h0 : kTHeads;
+            float sum[kTHeads];
+            trow_sum<EVEN>(pair, g.tperm, eb, ee, gl, g.nh, h0, nhb, tw_att, g.hs, g.e0, sum);
 #pragma unroll
-                        for (int b = 0; b < HB; b += 2) {
-                            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                            if (b < nhb) v = *reinterpret_cast<const float4*>(q + 2 * b);
-                            av[b] = v.x; dv[b] = v.y; av[b + 1] = v.z; dv[b + 1] = v.w;
-                        }
-                    } else {
-#pragma unroll
-                        for (int b = 0; b < HB; ++b) {
-                            float2 v = make_float2(0.f, 0.f);
-                            if (b < nhb) v = *reinterpret_cast<const float2*>(q + 2 * b);
-                            av[b] = v.x; dv[b] = v.y;
-                        }
-                    }
-#pragma unroll
-                    for (int b = 0; b < HB; ++b)
-                        if (b < nhb) {
-                            tw_att[(h0 + b) * g.hs + e - g.e0] = av[b];
-                            sum[b] += dv[b];
-                        }
-                }
-#pragma unroll
-                for (int b = 0; b < HB; ++b) {
-#pragma unroll
-                    for (int m = 1; m < GW; m <<= 1) sum[b] += __shfl_xor(sum[b], m, kWave);
-                    if (gl == 0 && b < nhb && ee > eb) {
-                        const int64_t r = i < g.n_own ? g.base_row + i : (int64_t)g.bnd[i - g.n_own];
-                        gs_src[r * g.nh + h0 + b] += sum[b];
-                    }
-                }
-            }
+            for (int b = 0; b < kTHeads; ++b)
+                if (gl == 0 && b < nhb) gs_src[r * g.nh + h0 + b] += sum[b];
         }
     }
+}
+
+// The same over the whole graph's transpose (MergedItems): gs_src of a row is the sum over its
+// pieces in order, stored once.  A group of 16 lanes takes a row of at most one segment, piece by
+// piece, or one unit of a longer row.
+template <bool EVEN>
+__global__ __launch_bounds__(kBlock) void k_gat_merged_rows(const MergedItems it, const float* __restrict__ pair,
+                                                            float* __restrict__ tw_att, float* __restrict__ gs_src,
+                                                            int32_t nh, int64_t hs, float* __restrict__ stat)
+{
+    const int lane = threadIdx.x % kWave, gl = lane % kGroup, grp = lane / kGroup;
+    const int64_t item = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kGroup;
+    if (item >= it.nunits + it.nrows) return;
+    float sum[kTHeads];
+    if (item < it.nunits) {
+        const int64_t eb = it.unit_begin[item], ee = eb + (it.unit_len[item] & 0xFFFF);
+        for (int32_t h0 = 0; h0 < nh; h0 += kTHeads) {
+            const int nhb = nh - h0 < kTHeads ? nh - h0 : kTHeads;
+            trow_sum<EVEN>(pair, it.perm, eb, ee, gl, nh, h0, nhb, tw_att, hs, 0, sum);
+#pragma unroll
+            for (int b = 0; b < kTHeads; ++b)
+                if (gl == 0 && b < nhb) stat[(int64_t)(h0 + b) * it.nunits + item] = sum[b];
+        }
+        return;
+    }
+    const int32_t row = it.rows[item - it.nunits] & 0x7FFFFFFF;
+    const int64_t r_end = it.rp[row + 1];
+    for (int32_t h0 = 0; h0 < nh; h0 += kTHeads) {
+        const int nhb = nh - h0 < kTHeads ? nh - h0 : kTHeads;
+        float tot[kTHeads] = {0.f, 0.f, 0.f, 0.f};
+        for (int64_t e = it.rp[row]; e < r_end;) {
+            int64_t pe = e;
+            for (;;) {                                   // end of this piece (the row's last entry ends one)
+                const bool end = pe + gl < r_end && it.col[pe + gl] < 0;
+                const unsigned ends = (unsigned)(__ballot(end) >> (grp * kGroup)) & 0xFFFFu;
+                if (ends) { pe += __ffs((int)ends); break; }
+                pe += kGroup;
+                if (pe >= r_end) { pe = r_end; break; }
+            }
+            trow_sum<EVEN>(pair, it.perm, e, pe, gl, nh, h0, nhb, tw_att, hs, 0, sum);
+#pragma unroll
+            for (int b = 0; b < kTHeads; ++b) tot[b] += sum[b];
+            e = pe;
+        }
+#pragma unroll
+        for (int b = 0; b < kTHeads; ++b)
+            if (gl == 0 && b < nhb) gs_src[(int64_t)row * nh + h0 + b] = tot[b];
+    }
+}
+// the longer rows from their units: a piece of several units as k_gat_tcombine adds segments
+__global__ __launch_bounds__(kBlock) void k_gat_merged_combine(const MergedItems it, const float* __restrict__ stat,
+                                                               float* __restrict__ gs_src, int32_t nh)
+{
+    const int t = threadIdx.x % kWave;
+    const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    if (i >= it.nlong * nh) return;
+    const int32_t h = (int32_t)(i % nh);
+    const int64_t li = i / nh;
+    const int64_t row = it.long_row[li] & 0x7FFFFFFF;
+    const int64_t first = it.long_first[li];
+    const int32_t nu = it.long_nunits[li];
+    const float* st = stat + (int64_t)h * it.nunits + first;
+    float tot = 0.f;
+    for (int32_t u = 0; u < nu;) {
+        // units u .. ue - 1 are one piece
+        int32_t ue = u;
+        for (;;) {
+            const bool end = ue + t < nu && it.unit_len[first + ue + t] < 0;
+            const unsigned long long ends = __ballot(end);
+            if (ends) { ue += __ffsll((unsigned long long)ends); break; }
+            ue += kWave;
+            if (ue >= nu) { ue = nu; break; }
+        }
+        if (ue == u + 1) {
+            tot += st[u];
+        } else {
+            float v = 0.f;
+            for (int32_t j = u + t; j < ue; j += kWave) v += st[j];
+            tot += wave_sum(v);
+        }
+        u = ue;
+    }
+    if (t == 0) gs_src[row * nh + h] = tot;
 }
 
 // Edge-wise dot products: dal[e - e0] = dY[row,:] . src(col[e])[:] with src the partition's own
@@ -921,72 +996,88 @@ __global__ __launch_bounds__(kBlock) void k_gat_dots(GatDotArgs g)
 }
 
 // gH[r, j] += gs_src[r nh] a_src[j] + gs_dst[r nh] a_dst[j] for the rows of one partition (one
-// head: its scores are nh floats apart), and the
-// per-block partial column sums  sum_r gs_src[r] H[r, j]  (first f columns of `partial` rows) and
-// sum_r gs_dst[r] H[r, j]  (next f columns), 256 rows per block.
+// head: its scores are nh floats apart), and the per-block partial column sums
+// sum_r gs_src[r] H[r, j] (first f columns of `partial` rows) and sum_r gs_dst[r] H[r, j] (next f
+// columns), 256 rows per block.  Bound by memory: one read of H, one read and write of gH.  A thread
+// takes four columns (a 16-byte vector; H and gH have rows of ld floats, a multiple of 4, zeros
+// past f) of every (256 / vectors per row)-th row with four rows in flight; the row groups are
+// combined through LDS in order.  (One thread per column, one row after the other: 115 us on 9,400
+// rows of 256 columns.)  The four columns of a vector belong to one head.
 __global__ __launch_bounds__(kBlock) void k_gat_rank1(float* __restrict__ gH, const float* __restrict__ H,
                                                       int32_t ld, int32_t f, int64_t rows,
                                                       const float* __restrict__ gs_src,
                                                       const float* __restrict__ gs_dst,
                                                       const float* __restrict__ a_src,
                                                       const float* __restrict__ a_dst,
-                                                      float* __restrict__ partial, int32_t nh, int32_t fh)
+                                                      float* __restrict__ partial, int32_t nh, int32_t fh,
+                                                      const int2* __restrict__ blk)
 {
-    const int64_t r0 = (int64_t)blockIdx.x * 256;
-    const int64_t r1 = r0 + 256 < rows ? r0 + 256 : rows;
-    for (int32_t j = threadIdx.x; j < f; j += kBlock) {
-        const float as = a_src[j], ad = a_dst[j];
-        float p1 = 0.f, p2 = 0.f;
-        for (int64_t r = r0; r < r1; ++r) {
-            const float gs = gs_src[r * nh + j / fh], gd = gs_dst[r * nh + j / fh];
-            const float h = H[r * ld + j];
-            gH[r * ld + j] += gs * as + gd * ad;
-            p1 += gs * h;
-            p2 += gd * h;
-        }
-        partial[(int64_t)blockIdx.x * 2 * f + j] = p1;
-        partial[(int64_t)blockIdx.x * 2 * f + f + j] = p2;
+    constexpr int U = 4;
+    __shared__ float4 sm[kBlock][2];
+    int64_t r0 = (int64_t)blockIdx.x * 256;
+    int64_t r1 = r0 + 256 < rows ? r0 + 256 : rows;
+    if (blk) {
+        r0 = blk[blockIdx.x].x;
+        r1 = blk[blockIdx.x].y;
     }
-}
-
-// The same for rows of at most CW <= 128 columns: the 256 threads form kBlock / CW row groups of
-// CW columns, each group takes every (kBlock / CW)-th row of the block's 256, and the groups'
-// partial column sums are combined in group order.
-template <int CW>
-__global__ __launch_bounds__(kBlock) void k_gat_rank1_narrow(float* __restrict__ gH, const float* __restrict__ H,
-                                                             int32_t ld, int32_t f, int64_t rows,
-                                                             const float* __restrict__ gs_src,
-                                                             const float* __restrict__ gs_dst,
-                                                             const float* __restrict__ a_src,
-                                                             const float* __restrict__ a_dst,
-                                                             float* __restrict__ partial, int32_t nh, int32_t fh)
-{
-    constexpr int RG = kBlock / CW;
-    __shared__ float sm[RG][CW][2];
-    const int j = threadIdx.x % CW, rgp = threadIdx.x / CW;
-    const int64_t r0 = (int64_t)blockIdx.x * 256;
-    const int64_t r1 = r0 + 256 < rows ? r0 + 256 : rows;
-    float p1 = 0.f, p2 = 0.f;
-    if (j < f) {
-        const float as = a_src[j], ad = a_dst[j];
-        for (int64_t r = r0 + rgp; r < r1; r += RG) {
-            const float gs = gs_src[r * nh + j / fh], gd = gs_dst[r * nh + j / fh];
-            const float h = H[r * ld + j];
-            gH[r * ld + j] += gs * as + gd * ad;
-            p1 += gs * h;
-            p2 += gd * h;
+    const int cw = (f + 3) / 4;
+    for (int cc = 0; cc < cw; cc += kBlock) {
+        const int cwe = cw - cc < kBlock ? cw - cc : kBlock;
+        const int rpp = kBlock / cwe, rsub = threadIdx.x / cwe;
+        const int j = 4 * (cc + (int)threadIdx.x % cwe);
+        float4 p1 = make_float4(0.f, 0.f, 0.f, 0.f), p2 = p1;
+        if (rsub < rpp) {
+            float as[4], ad[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                as[e] = j + e < f ? a_src[j + e] : 0.f;
+                ad[e] = j + e < f ? a_dst[j + e] : 0.f;
+            }
+            const int32_t hd = j / fh;
+            for (int64_t r = r0 + rsub; r < r1; r += (int64_t)rpp * U) {
+                float gs[U], gd[U];
+                float4 h[U], g[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t rr = r + (int64_t)u * rpp < r1 ? r + (int64_t)u * rpp : r;
+                    gs[u] = gs_src[rr * nh + hd];
+                    gd[u] = gs_dst[rr * nh + hd];
+                    h[u] = *reinterpret_cast<const float4*>(H + rr * ld + j);
+                    g[u] = *reinterpret_cast<const float4*>(gH + rr * ld + j);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t rr = r + (int64_t)u * rpp;
+                    if (rr >= r1) break;
+                    g[u].x += gs[u] * as[0] + gd[u] * ad[0];
+                    g[u].y += gs[u] * as[1] + gd[u] * ad[1];
+                    g[u].z += gs[u] * as[2] + gd[u] * ad[2];
+                    g[u].w += gs[u] * as[3] + gd[u] * ad[3];
+                    *reinterpret_cast<float4*>(gH + rr * ld + j) = g[u];
+                    p1.x += gs[u] * h[u].x; p1.y += gs[u] * h[u].y; p1.z += gs[u] * h[u].z; p1.w += gs[u] * h[u].w;
+                    p2.x += gd[u] * h[u].x; p2.y += gd[u] * h[u].y; p2.z += gd[u] * h[u].z; p2.w += gd[u] * h[u].w;
+                }
+            }
         }
-    }
-    sm[rgp][j][0] = p1;
-    sm[rgp][j][1] = p2;
-    __syncthreads();
-    if (rgp == 0 && j < f) {
-        for (int q = 1; q < RG; ++q) {
-            p1 += sm[q][j][0];
-            p2 += sm[q][j][1];
+        sm[threadIdx.x][0] = p1;
+        sm[threadIdx.x][1] = p2;
+        __syncthreads();
+        if (rsub == 0) {
+            for (int q = 1; q < rpp; ++q) {
+                const float4 o1 = sm[q * cwe + threadIdx.x][0], o2 = sm[q * cwe + threadIdx.x][1];
+                p1.x += o1.x; p1.y += o1.y; p1.z += o1.z; p1.w += o1.w;
+                p2.x += o2.x; p2.y += o2.y; p2.z += o2.z; p2.w += o2.w;
+            }
+            const float s1[4] = {p1.x, p1.y, p1.z, p1.w}, s2[4] = {p2.x, p2.y, p2.z, p2.w};
+            float* out = partial + (int64_t)blockIdx.x * 2 * f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j + e < f) {
+                    out[j + e] = s1[e];
+                    out[f + j + e] = s2[e];
+                }
         }
-        partial[(int64_t)blockIdx.x * 2 * f + j] = p1;
-        partial[(int64_t)blockIdx.x * 2 * f + f + j] = p2;
+        __syncthreads();
     }
 }
 
@@ -1108,8 +1199,9 @@ void launch_gat_transposed(const int64_t* trp, const int32_t* tperm, int64_t e0,
         q.seg_row = items.seg_row; q.seg_begin = items.seg_begin; q.seg_len = items.seg_len; q.nsegs = items.nsegs;
         q.long_row = items.long_row; q.long_first = items.long_first; q.long_nseg = items.long_nseg;
         q.nlong = items.nlong;
-        hipLaunchKernelGGL(k_gat_tsegs, dim3((unsigned)((q.nsegs + 3) / 4)), dim3(kBlock), 0, s, g, q, pair, tw_att,
-                           segwork);
+        const dim3 grid((unsigned)((q.nsegs * kGroup + kBlock - 1) / kBlock));
+        if (nh % 2 == 0) hipLaunchKernelGGL((k_gat_tsegs<true>), grid, dim3(kBlock), 0, s, g, q, pair, tw_att, segwork);
+        else hipLaunchKernelGGL((k_gat_tsegs<false>), grid, dim3(kBlock), 0, s, g, q, pair, tw_att, segwork);
         hipLaunchKernelGGL(k_gat_tcombine, dim3((unsigned)((q.nlong + 3) / 4)), dim3(kBlock), 0, s, g, q,
                            (const float*)segwork, gs_src);
     }
@@ -1143,21 +1235,25 @@ int64_t gat_rank1_partial_floats(int64_t rows, int32_t f) { return ((rows + 255)
 
 void launch_gat_rank1(float* gH, const float* H, int32_t ld, int32_t f, int64_t rows, const float* gs_src,
                       const float* gs_dst, int32_t nh, int32_t fh, const float* a_src, const float* a_dst,
-                      float* partial, hipStream_t s)
+                      float* partial, hipStream_t s, const RowBlocks* rb)
 {
     if (rows <= 0) return;
-    const dim3 grid((unsigned)((rows + 255) / 256)), b(kBlock);
-    if (f <= 32)
-        hipLaunchKernelGGL((k_gat_rank1_narrow<32>), grid, b, 0, s, gH, H, ld, f, rows, gs_src, gs_dst, a_src, a_dst,
-                           partial, nh, fh);
-    else if (f <= 64)
-        hipLaunchKernelGGL((k_gat_rank1_narrow<64>), grid, b, 0, s, gH, H, ld, f, rows, gs_src, gs_dst, a_src, a_dst,
-                           partial, nh, fh);
-    else if (f <= 128)
-        hipLaunchKernelGGL((k_gat_rank1_narrow<128>), grid, b, 0, s, gH, H, ld, f, rows, gs_src, gs_dst, a_src, a_dst,
-                           partial, nh, fh);
-    else
-        hipLaunchKernelGGL(k_gat_rank1, grid, b, 0, s, gH, H, ld, f, rows, gs_src, gs_dst, a_src, a_dst, partial, nh, fh);
+    const dim3 grid((unsigned)(rb ? rb->nblocks : (rows + 255) / 256)), b(kBlock);
+    hipLaunchKernelGGL(k_gat_rank1, grid, b, 0, s, gH, H, ld, f, rows, gs_src, gs_dst, a_src, a_dst, partial, nh, fh,
+                       rb ? rb->rows : (const int2*)nullptr);
+}
+
+void launch_gat_merged(const MergedItems& it, const float* pair, float* tw_att, float* gs_src, int32_t nh, int64_t hs,
+                       float* stat, hipStream_t s)
+{
+    const int64_t items = it.nunits + it.nrows;
+    if (items <= 0) return;
+    const dim3 grid((unsigned)((items * kGroup + kBlock - 1) / kBlock)), b(kBlock);
+    if (nh % 2 == 0) hipLaunchKernelGGL((k_gat_merged_rows<true>), grid, b, 0, s, it, pair, tw_att, gs_src, nh, hs, stat);
+    else hipLaunchKernelGGL((k_gat_merged_rows<false>), grid, b, 0, s, it, pair, tw_att, gs_src, nh, hs, stat);
+    if (it.nlong > 0)
+        hipLaunchKernelGGL(k_gat_merged_combine, dim3((unsigned)((it.nlong * nh + 3) / 4)), b, 0, s, it,
+                           (const float*)stat, gs_src, nh);
 }
 
 }  // namespace gnnmi

@@ -31,9 +31,11 @@ __global__ __launch_bounds__(kBlock) void k_merge_count(int64_t nrows, int32_t k
 // one wavefront per row of partition p's transpose
 __global__ __launch_bounds__(kBlock) void k_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* __restrict__ bnd,
                                                        const int64_t* __restrict__ trp, const int32_t* __restrict__ tcol,
-                                                       const float* __restrict__ tw, const int64_t* __restrict__ rp,
+                                                       const float* __restrict__ tw, const int32_t* __restrict__ tperm,
+                                                       int64_t fwd0, const int64_t* __restrict__ rp,
                                                        int64_t* __restrict__ cursor, int32_t* __restrict__ col,
-                                                       float* __restrict__ w, uint8_t* __restrict__ self_first)
+                                                       float* __restrict__ w, int32_t* __restrict__ perm,
+                                                       uint8_t* __restrict__ self_first)
 {
     const int lane = threadIdx.x % kWave;
     const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
@@ -46,7 +48,8 @@ __global__ __launch_bounds__(kBlock) void k_merge_fill(int64_t r0, int64_t np, i
         uint32_t c = (uint32_t)(tcol[e0 + j] + (int32_t)r0);
         if (j == len - 1) c |= kPieceEnd | (self ? kSelfNext : 0u);
         col[at + j] = (int32_t)c;
-        w[at + j] = tw[e0 + j];
+        if (tw) w[at + j] = tw[e0 + j];
+        else perm[at + j] = (int32_t)(fwd0 + tperm[e0 + j]);
     }
     if (lane == 0) {
         cursor[u] = at + len;
@@ -196,12 +199,12 @@ void launch_merge_count(int64_t nrows, int32_t k, const int64_t* toff, const int
 }
 
 void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, const int64_t* trp, const int32_t* tcol,
-                       const float* tw, const int64_t* rp, int64_t* cursor, int32_t* col, float* w, uint8_t* self_first,
-                       hipStream_t s)
+                       const float* tw, const int32_t* tperm, int64_t e0, const int64_t* rp, int64_t* cursor, int32_t* col,
+                       float* w, int32_t* perm, uint8_t* self_first, hipStream_t s)
 {
     if (np + nb > 0)
-        hipLaunchKernelGGL(k_merge_fill, per_wave(np + nb), dim3(kBlock), 0, s, r0, np, nb, bnd, trp, tcol, tw, rp, cursor,
-                           col, w, self_first);
+        hipLaunchKernelGGL(k_merge_fill, per_wave(np + nb), dim3(kBlock), 0, s, r0, np, nb, bnd, trp, tcol, tw, tperm, e0, rp,
+                           cursor, col, w, perm, self_first);
 }
 
 void launch_merge_mask_count(int64_t n, const int64_t* rp, const int32_t* col, const uint8_t* mask, int32_t* cnt,

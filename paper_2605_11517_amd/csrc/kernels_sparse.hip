@@ -1005,6 +1005,7 @@ struct MergedArgs {
     const void* src;
     float* out;
     int32_t d, ld;
+    int64_t wss = 0;        // entry weights of column slice s start at w + s wss
 };
 
 template <typename TIn, int G, int UNR, bool SELF>
@@ -1019,6 +1020,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_merged(const MergedArgs g, int3
     const int raw = (int)(blk % (unsigned)nslices) * (G * EPV) + gl * EPV;
     const bool live = raw < g.d;
     const int coff = live ? raw : 0;
+    const float* wsl = g.it.w + (int64_t)(blk % (unsigned)nslices) * g.wss;
     blk /= (unsigned)nslices;
     const int64_t item = ((int64_t)blk * (kBlock / kWave) + threadIdx.x / kWave) * S + slot;
     const TIn* src = static_cast<const TIn*>(g.src);
@@ -1063,14 +1065,14 @@ __global__ __launch_bounds__(kBlock) void k_spmm_merged(const MergedArgs g, int3
     float nx_w = 0.f;
     if (gl < len) {
         nx_c = g.it.col[e_begin + gl];
-        nx_w = g.it.w[e_begin + gl];
+        nx_w = wsl[e_begin + gl];
     }
     for (int32_t e0 = 0; e0 < maxlen; e0 += G) {
         const int32_t my_c = nx_c;
         const float my_w = nx_w;
         if (e0 + G + gl < len) {
             nx_c = g.it.col[e_begin + e0 + G + gl];
-            nx_w = g.it.w[e_begin + e0 + G + gl];
+            nx_w = wsl[e_begin + e0 + G + gl];
         }
         const int cnt = len - e0;
         const int lead_cnt = maxlen - e0 < G ? maxlen - e0 : G;
@@ -1554,7 +1556,7 @@ bool launch_spmm_heads(const int64_t* rp, const int32_t* col, const float* w, in
 
 namespace {
 template <typename TIn>
-void spmm_merged_typed(const MergedArgs& g0, int self, hipStream_t s)
+void spmm_merged_typed(const MergedArgs& g0, int self, int32_t heads, hipStream_t s)
 {
     constexpr int EPV = Elem<TIn>::EPV;
     MergedArgs g = g0;
@@ -1564,7 +1566,8 @@ void spmm_merged_typed(const MergedArgs& g0, int self, hipStream_t s)
     const int nvec = (d + EPV - 1) / EPV;
     if (d % EPV == 0) {
         // slots of 4 to 32 vectors; wider rows in column slices of 256 bytes (see spmm_typed)
-        const int G = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 16;
+        // (several heads: a slice is a head)
+        const int G = heads > 1 ? nvec / heads : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 16;
         const int ns = (nvec + G - 1) / G;
         const int S = kWave / G;
         const int64_t blocks = (n_items + (int64_t)wpb * S - 1) / ((int64_t)wpb * S);
@@ -1611,22 +1614,27 @@ void spmm_merged_typed(const MergedArgs& g0, int self, hipStream_t s)
 }
 }  // namespace
 
-void launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
-                        int self, hipStream_t s)
+bool launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, float* out, int32_t d,
+                        int self, hipStream_t s, int32_t ld, int32_t heads, int64_t wss)
 {
-    if (d <= 0 || it.nunits + it.nrows <= 0) return;
-    MergedArgs g{it, src, out, d, d};
-    if (in_bf16) spmm_merged_typed<uint16_t>(g, self, s);
-    else spmm_merged_typed<float>(g, self, s);
+    if (d <= 0 || it.nunits + it.nrows <= 0) return true;
+    if (heads > 1) {
+        const int32_t f = d / heads;
+        if (in_bf16 || d % heads != 0 || !(f == 16 || f == 32 || f == 64 || f == 128)) return false;
+    }
+    MergedArgs g{it, src, out, d, ld > 0 ? ld : d, wss};
+    if (in_bf16) spmm_merged_typed<uint16_t>(g, self, heads, s);
+    else spmm_merged_typed<float>(g, self, heads, s);
+    return true;
 }
 
-void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s)
+void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s, int32_t ld)
 {
     if (it.nlong <= 0 || d <= 0) return;
-    MergedArgs g{it, nullptr, out, d, d};
+    MergedArgs g{it, nullptr, out, d, ld > 0 ? ld : d, 0};
     const int wpb = kBlock / kWave;
     const dim3 grid((unsigned)((it.nlong + wpb - 1) / wpb), (unsigned)((d + 255) / 256));
-    if (d % 4 == 0) {
+    if (d % 4 == 0 && g.ld % 4 == 0) {
         if (self) hipLaunchKernelGGL((k_spmm_merged_reduce<true, true>), grid, dim3(kBlock), 0, s, g);
         else hipLaunchKernelGGL((k_spmm_merged_reduce<true, false>), grid, dim3(kBlock), 0, s, g);
     } else {

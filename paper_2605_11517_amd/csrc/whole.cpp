@@ -30,7 +30,7 @@ constexpr int64_t kWholeLimitBytes = (int64_t)40 << 30;
 void free_merged(DevMeta::Merged& m)
 {
     for (void* p : {(void*)m.rp, (void*)m.col, (void*)m.w, (void*)m.rows, (void*)m.unit_begin, (void*)m.unit_len,
-                    (void*)m.long_row, (void*)m.long_first, (void*)m.long_nunits, (void*)m.partial, (void*)m.self_first})
+                    (void*)m.long_row, (void*)m.long_first, (void*)m.long_nunits, (void*)m.partial, (void*)m.self_first, (void*)m.perm})
         if (p) (void)hipFree(p);
     m = DevMeta::Merged{};
 }
@@ -240,7 +240,8 @@ void finish_rows(const gnn_ctx* c, DevMeta::Merged& m, const int32_t* cnt_dev)
     m.rows = to_device(rows);
     m.long_row = to_device(longs);
     m.col = device_array<int32_t>(m.entries);
-    m.w = device_array<float>(m.entries);
+    if (c->model == GNN_GAT) m.perm = device_array<int32_t>(m.entries);
+    else m.w = device_array<float>(m.entries);
 }
 
 // Units of the long rows, room for their sums, and the self-term marks of both lists.
@@ -276,7 +277,7 @@ void finish_units(const gnn_ctx* c, DevMeta::Merged& m, int32_t width)
 int32_t transposed_width(const gnn_ctx* c)
 {
     int32_t d = 4;
-    for (int32_t l = 1; l <= c->L; ++l) d = std::max(d, c->transform_first(l) ? c->padded(l) : c->dims[(size_t)l - 1]);
+    for (int32_t l = 1; l <= c->L; ++l) d = std::max(d, c->transform_first(l) ? c->hrow(l) : c->dims[(size_t)l - 1]);
     return d;
 }
 
@@ -303,7 +304,8 @@ void build_merged(const gnn_ctx* c, DevMeta::Merged& m)
         const int32_t p = M.sched[(size_t)t];
         const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;
         launch_merge_fill(r0, np, M.boff[(size_t)p + 1] - M.boff[(size_t)p], c->D.bnd + M.boff[(size_t)p],
-                          c->D.trp + M.toff[(size_t)p], c->D.tcol, c->D.tw, m.rp, cursor, m.col, m.w, m.self_first, nullptr);
+                          c->D.trp + M.toff[(size_t)p], c->D.tcol, c->D.tw, c->D.tperm, M.rp[(size_t)r0], m.rp, cursor,
+                          m.col, m.w, m.perm, m.self_first, nullptr);
     }
     check(hipGetLastError());
     finish_units(c, m, transposed_width(c));
@@ -333,8 +335,8 @@ bool wanted(const gnn_ctx* c)
     // GNNMI_WHOLE=0: partition by partition (for measurements and tests; read per call)
     const char* e = std::getenv("GNNMI_WHOLE");
     if (e && e[0] == '0') return false;
-    return c->built && !c->is_whole && !c->streaming() && c->M.k > 1 && c->model != GNN_GAT &&
-           c->M.n + c->M.stats.sum_boundary < ((int64_t)1 << 30) && c->M.n <= kWholeMaxRows;
+    return c->built && !c->is_whole && !c->streaming() && c->M.k > 1 &&
+           c->M.stats.nnz < ((int64_t)1 << 31) && c->M.n + c->M.stats.sum_boundary < ((int64_t)1 << 30) && c->M.n <= kWholeMaxRows;
 }
 
 void copy_settings(const gnn_ctx* c, gnn_ctx* w)
@@ -512,14 +514,20 @@ bool whole_runs(const gnn_ctx* c)
     return !(e && e[0] == '0');
 }
 
-void run_spmm_merged(gnn_ctx* c, int32_t layer, const void* src, float* out, int32_t d, int self, hipStream_t s)
+MergedItems merged_items(const DevMeta::Merged& m)
 {
-    const DevMeta::Merged& m = layer == c->L && c->D.merged_masked.ready ? c->D.merged_masked : c->D.merged;
     MergedItems it;
-    it.rp = m.rp; it.col = m.col; it.w = m.w; it.rows = m.rows; it.nrows = m.nrows;
+    it.rp = m.rp; it.col = m.col; it.w = m.w; it.perm = m.perm; it.rows = m.rows; it.nrows = m.nrows;
     it.unit_begin = m.unit_begin; it.unit_len = m.unit_len; it.nunits = m.nunits;
     it.long_row = m.long_row; it.long_first = m.long_first; it.long_nunits = m.long_nunits; it.nlong = m.nlong;
     it.partial = m.partial; it.avg_len = m.avg_len;
+    return it;
+}
+
+void run_spmm_merged(gnn_ctx* c, int32_t layer, const void* src, float* out, int32_t d, int self, hipStream_t s)
+{
+    const DevMeta::Merged& m = layer == c->L && c->D.merged_masked.ready ? c->D.merged_masked : c->D.merged;
+    const MergedItems it = merged_items(m);
     {
         Timed t(c, s, GNN_K_SPMM_T);
         launch_spmm_merged(it, src, c->bf16() ? 1 : 0, out, d, self, s);
@@ -545,6 +553,7 @@ gnn_status whole_epoch(gnn_ctx* c, void* stream, float* loss_out)
     std::fill(c->fwd_done.begin(), c->fwd_done.end(), done);
     std::fill(c->xf_bwd_done.begin(), c->xf_bwd_done.end(), done);
     std::fill(c->z_done.begin(), c->z_done.end(), done);
+    std::fill(c->att_done.begin(), c->att_done.end(), 0);
     std::fill(c->bwd_done.begin(), c->bwd_done.end(), done ? c->M.k : 0);
     c->loss_done = done != 0;
     if (st != GNN_OK) {

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from helpers import ring_of_blocks, small_graph
-from synth import features, glorot_weights, labels_and_mask, to_bf16_grid
+from synth import attention_vectors, features, glorot_weights, labels_and_mask, to_bf16_grid
 
 pytestmark = pytest.mark.gpu
 KEYS = ("act", "gact", "gW", "gWs", "gb")
@@ -33,6 +33,12 @@ CASES = [
     ("sage", (72, 136, 8), 2000, 16000, True, 3, "random", "bf16", "tuned"),
     ("gcn", (20, 50, 50, 7), 500, 3000, False, 2, "random", "bf16", "default"),     # odd widths
     ("gcn", (256, 264, 300, 16), 10000, 60000, True, 3, "random", "bf16", "default"),  # 256 x 256 tiles, ragged ends
+    # attention; the model's heads per layer behind the colon
+    ("gat:1x1x1", (24, 260, 30, 7), 3000, 40000, True, 5, "lp", "f32", "tuned"),
+    ("gat:8x8x1", (100, 256, 256, 47), 3000, 60000, True, 4, "lp", "f32", "tuned"),  # heads side by side, in slots
+    ("gat:3x2x1", (20, 36, 24, 7), 2500, 90000, True, 6, "random", "f32", "default"),  # side by side, head by head; hubs
+    ("gat:4x5x1", (20, 20, 15, 7), 900, 7000, False, 7, "random", "f32", "default"),   # five and three columns a head
+    ("gat:8x1", (16, 16, 5), 300, 900, True, 60, "random", "f32", "tuned"),
 ]
 
 
@@ -41,6 +47,7 @@ def test_whole_graph_epoch_gives_the_bits_of_the_partition_by_partition_epoch(mo
     model, dims, n, m_draw, sym, k, mode, dtype, switches = case
     print("case whole %s" % (case,), flush=True)
     from paper_2605_11517_amd import Session
+    model, _, heads = model.partition(":")
     user = None
     if mode == "ring":
         rowptr, colidx, user, _ = ring_of_blocks(k, n // k, seed=4)
@@ -53,6 +60,10 @@ def test_whole_graph_epoch_gives_the_bits_of_the_partition_by_partition_epoch(mo
     y, _ = labels_and_mask(n, dims[-1], 0.5, 5)
     m = (np.random.default_rng(6).random(n) < 0.3).astype(np.uint8)
     w = glorot_weights(dims, 5, sage=(model == "sage"), bias_scale=0.1)
+    if model == "gat":
+        attention_vectors(w, 5)
+        for layer, h in zip(w, heads.split("x")):
+            layer["heads"] = int(h)
     if dtype == "bf16":
         X = to_bf16_grid(X)
     kw = {"tuned": dict(layer_order="auto", fuse_gather=True, masked_backward=True, keep_forward=True),
