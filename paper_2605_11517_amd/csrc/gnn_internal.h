@@ -193,8 +193,9 @@ struct MergedItems {
     const int32_t* col = nullptr;     // destination row | flags
     const float* w = nullptr;
     const int32_t* perm = nullptr;    // attention: position of the entry in the forward operator
-    const int32_t* rows = nullptr;    // rows of at most `segment` entries, longest first; top bit: the
-    int64_t nrows = 0;                // self term comes before every piece
+    const int32_t* rows = nullptr;    // rows summed by one slot (no piece longer than a segment, at most
+    int64_t nrows = 0;                // merged_row_max() entries), longest first; top bit: the self term
+                                      // comes before every piece
     // longer rows: units (pieces, or segments of a piece) summed on their own and combined per row
     const int64_t* unit_begin = nullptr;
     const int32_t* unit_len = nullptr;   // entries | 1 << 31: last of its piece | 1 << 30: self term next
@@ -219,9 +220,11 @@ bool launch_spmm_merged(const MergedItems& it, const void* src, int in_bf16, flo
 void launch_spmm_merged_reduce(const MergedItems& it, float* out, int32_t d, int self, hipStream_t s, int32_t ld = 0);
 
 // Building it on the device (kernels_merge.hip) from the per-partition transposes.
-// cnt[u] += entries of every row of every T_p^T that belongs to vertex u
+// cnt[u] += entries of every row of every T_p^T that belongs to vertex u; kLongPiece is set where one of
+// them has more than `segment`
+constexpr uint32_t kLongPiece = 0x80000000u;
 void launch_merge_count(int64_t nrows, int32_t k, const int64_t* toff, const int64_t* off, const int64_t* boff,
-                        const int32_t* bnd, const int64_t* trp, int32_t* cnt, hipStream_t s);
+                        const int32_t* bnd, const int64_t* trp, int32_t* cnt, int32_t segment, hipStream_t s);
 // appends partition p's piece of every row at cursor[row]; self_first (may be null): marks for
 // GraphSAGE's self term
 // tw -> w, or (attention) tperm + e0 -> perm
@@ -230,7 +233,7 @@ void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, c
                        float* w, int32_t* perm, uint8_t* self_first, hipStream_t s);
 // the operator restricted to destinations with mask != 0: entries kept per row, then the entries
 void launch_merge_mask_count(int64_t n, const int64_t* rp, const int32_t* col, const uint8_t* mask, int32_t* cnt,
-                             hipStream_t s);
+                             int32_t segment, hipStream_t s);
 void launch_merge_mask_fill(int64_t n, const int64_t* rp, const int32_t* col, const float* w, const uint8_t* mask,
                             const int64_t* out_rp, int32_t* out_col, float* out_w, const uint8_t* self_in,
                             uint8_t* self_out, hipStream_t s);

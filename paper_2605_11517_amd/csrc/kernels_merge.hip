@@ -12,7 +12,7 @@ constexpr int kWave = 64;
 __global__ __launch_bounds__(kBlock) void k_merge_count(int64_t nrows, int32_t k, const int64_t* __restrict__ toff,
                                                         const int64_t* __restrict__ off, const int64_t* __restrict__ boff,
                                                         const int32_t* __restrict__ bnd, const int64_t* __restrict__ trp,
-                                                        int32_t* __restrict__ cnt)
+                                                        int32_t* __restrict__ cnt, int32_t segment)
 {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= nrows) return;
@@ -26,6 +26,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_count(int64_t nrows, int32_t k
     const int64_t u = i < np ? off[lo] + i : (int64_t)bnd[boff[lo] + i - np];
     const int32_t len = (int32_t)(trp[j + 1] - trp[j]);
     if (len > 0) atomicAdd(&cnt[u], len);         // integers: any order gives the same count
+    if (len > segment) atomicOr(&cnt[u], (int32_t)kLongPiece);
 }
 
 // one wavefront per row of partition p's transpose
@@ -63,18 +64,34 @@ __global__ __launch_bounds__(kBlock) void k_merge_fill(int64_t r0, int64_t np, i
 
 __global__ __launch_bounds__(kBlock) void k_merge_mask_count(int64_t n, const int64_t* __restrict__ rp,
                                                              const int32_t* __restrict__ col,
-                                                             const uint8_t* __restrict__ mask, int32_t* __restrict__ cnt)
+                                                             const uint8_t* __restrict__ mask, int32_t* __restrict__ cnt,
+                                                             int32_t segment)
 {
     const int lane = threadIdx.x % kWave;
     const int64_t u = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     if (u >= n) return;
     const int64_t e1 = rp[u + 1];
-    int32_t c = 0;
+    int32_t c = 0, piece = 0;                     // entries kept: of the row, of the piece so far
+    bool long_piece = false;
     for (int64_t e = rp[u]; e < e1; e += kWave) {
-        const bool on = e + lane < e1 && mask[col[e + lane] & kMergedColumn] != 0;
-        c += __popcll(__ballot(on));
+        const int32_t v = e + lane < e1 ? col[e + lane] : 0;
+        const unsigned long long on = __ballot(e + lane < e1 && mask[v & kMergedColumn] != 0);
+        unsigned long long ends = __ballot(v < 0);
+        c += __popcll(on);
+        int from = 0;
+        while (ends) {                            // pieces that end in this chunk
+            const int at = __ffsll((unsigned long long)ends) - 1;
+            ends &= ends - 1;
+            const unsigned long long upto = at == 63 ? ~0ull : (1ull << (at + 1)) - 1ull;
+            piece += __popcll(on & upto & ~((1ull << from) - 1ull));
+            long_piece = long_piece || piece > segment;
+            piece = 0;
+            from = at + 1;
+            if (from == 64) break;
+        }
+        if (from < 64) piece += __popcll(on & ~((1ull << from) - 1ull));
     }
-    if (lane == 0) cnt[u] = c;
+    if (lane == 0) cnt[u] = c | (long_piece ? (int32_t)kLongPiece : 0);
 }
 
 // end of the piece that starts at e (the position after its last entry)
@@ -192,10 +209,11 @@ dim3 per_wave(int64_t n) { return dim3((unsigned)((n + kBlock / kWave - 1) / (kB
 }  // namespace
 
 void launch_merge_count(int64_t nrows, int32_t k, const int64_t* toff, const int64_t* off, const int64_t* boff,
-                        const int32_t* bnd, const int64_t* trp, int32_t* cnt, hipStream_t s)
+                        const int32_t* bnd, const int64_t* trp, int32_t* cnt, int32_t segment, hipStream_t s)
 {
     if (nrows > 0)
-        hipLaunchKernelGGL(k_merge_count, per_thread(nrows), dim3(kBlock), 0, s, nrows, k, toff, off, boff, bnd, trp, cnt);
+        hipLaunchKernelGGL(k_merge_count, per_thread(nrows), dim3(kBlock), 0, s, nrows, k, toff, off, boff, bnd, trp, cnt,
+                           segment);
 }
 
 void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, const int64_t* trp, const int32_t* tcol,
@@ -208,9 +226,9 @@ void launch_merge_fill(int64_t r0, int64_t np, int64_t nb, const int32_t* bnd, c
 }
 
 void launch_merge_mask_count(int64_t n, const int64_t* rp, const int32_t* col, const uint8_t* mask, int32_t* cnt,
-                             hipStream_t s)
+                             int32_t segment, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_merge_mask_count, per_wave(n), dim3(kBlock), 0, s, n, rp, col, mask, cnt);
+    hipLaunchKernelGGL(k_merge_mask_count, per_wave(n), dim3(kBlock), 0, s, n, rp, col, mask, cnt, segment);
 }
 
 void launch_merge_mask_fill(int64_t n, const int64_t* rp, const int32_t* col, const float* w, const uint8_t* mask,

@@ -940,12 +940,11 @@ __global__ __launch_bounds__(kBlock) void k_agg_gemm(const FusedArgs g)
 }
 
 // out[row,:] = rowscale[row] * (partial[first,:] + partial[first+1,:] + ...): one wavefront per
-// long row and 256-column block, segments added in ascending order (eight loads in flight per
-// lane).
+// long row and 256-column block, segments added in ascending order (32 loads in flight per lane).
 template <typename TOut, bool VEC>
 __global__ __launch_bounds__(kBlock) void k_spmm_long_reduce(const SpmmArgs g)
 {
-    constexpr int U = 8;
+    constexpr int U = 32;   // (8: 92-115 us for hubs of 10^3 segments)
     const int lane = threadIdx.x % kWave;
     const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     if (i >= g.it.nlong) return;
@@ -1008,12 +1007,12 @@ struct MergedArgs {
     int64_t wss = 0;        // entry weights of column slice s start at w + s wss
 };
 
-template <typename TIn, int G, int UNR, bool SELF>
+template <typename TIn, int G, bool SELF>
 __global__ __launch_bounds__(kBlock) void k_spmm_merged(const MergedArgs g, int32_t nslices)
 {
     constexpr int EPV = Elem<TIn>::EPV;
     constexpr int S = kWave / G;
-    constexpr int UNROLL = G < UNR ? G : UNR;
+    constexpr int UNROLL = 4;
     const int lane = threadIdx.x % kWave;
     const int slot = lane / G, gl = lane % G;
     unsigned blk = blockIdx.x;
@@ -1106,18 +1105,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_merged(const MergedArgs g, int3
                 }
             }
         };
-        if (UNR < 8) {
 #pragma unroll 1
-            for (int j0 = 0; j0 < G; j0 += UNROLL) {
-                if (j0 >= lead_cnt) break;           // uniform across the wavefront
-                batch(j0);
-            }
-        } else {
-#pragma unroll
-            for (int j0 = 0; j0 < G; j0 += UNROLL) {
-                if (j0 >= lead_cnt) break;           // uniform across the wavefront
-                batch(j0);
-            }
+        for (int j0 = 0; j0 < G; j0 += UNROLL) {
+            if (j0 >= lead_cnt) break;               // uniform across the wavefront
+            batch(j0);
         }
     }
     if (!live) return;
@@ -1194,11 +1185,12 @@ __global__ __launch_bounds__(kBlock) void k_spmm_merged_any(const MergedArgs g)
 }
 
 // out[row,:] of the rows longer than a segment from their units' sums: one wavefront per row and
-// 256-column block, sixteen loads in flight per lane
+// 256-column block, 32 loads in flight per lane (a hub of 10^5 entries has 10^3 units: its chain of
+// dependent batches is the shortest time the launch can take)
 template <bool VEC, bool SELF>
 __global__ __launch_bounds__(kBlock) void k_spmm_merged_reduce(const MergedArgs g)
 {
-    constexpr int W = VEC ? 4 : 1, U = VEC ? 16 : 4;
+    constexpr int W = VEC ? 4 : 1, U = VEC ? 32 : 8;
     const int lane = threadIdx.x % kWave;
     const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
     if (i >= g.it.nlong) return;
@@ -1565,26 +1557,29 @@ void spmm_merged_typed(const MergedArgs& g0, int self, int32_t heads, hipStream_
     const int32_t d = g.d;
     const int nvec = (d + EPV - 1) / EPV;
     if (d % EPV == 0) {
-        // slots of 4 to 32 vectors; wider rows in column slices of 256 bytes (see spmm_typed)
+        // Slots of 4 to 32 vectors.  Wider rows: column slices of 256 bytes where a row has many entries
+        // (the slices of a row run on different XCDs, see spmm_typed), whole wavefronts where it has
+        // few and the cost is per row and slice.  Measured (transposed pass, 16 / 32 / 64 vectors a
+        // slot): 256 fp32 columns, 55 entries a row 7.79 / 7.86 / 8.35 ms; 1024 bfloat16 columns, 27
+        // entries a row 1.95 / 1.77 / 1.64 ms.  Four loads in flight per slot: eight are no faster at
+        // 55 entries a row and 15-25 % slower below 30.
         // (several heads: a slice is a head)
-        const int G = heads > 1 ? nvec / heads : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 16;
+        const int wide = g.it.avg_len < short_rows_max() ? 64 : 16;
+        const int G = heads > 1 ? nvec / heads : nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : wide;
         const int ns = (nvec + G - 1) / G;
         const int S = kWave / G;
         const int64_t blocks = (n_items + (int64_t)wpb * S - 1) / ((int64_t)wpb * S);
         const dim3 grid((unsigned)(blocks * ns));
-        const bool few = g.it.avg_len < short_rows_max();
-#define GNN_MERGED(G, U)                                                                                          \
+#define GNN_MERGED(G)                                                                                             \
     do {                                                                                                          \
-        if (self) hipLaunchKernelGGL((k_spmm_merged<TIn, G, U, true>), grid, dim3(kBlock), 0, s, g, ns);          \
-        else hipLaunchKernelGGL((k_spmm_merged<TIn, G, U, false>), grid, dim3(kBlock), 0, s, g, ns);              \
+        if (self) hipLaunchKernelGGL((k_spmm_merged<TIn, G, true>), grid, dim3(kBlock), 0, s, g, ns);             \
+        else hipLaunchKernelGGL((k_spmm_merged<TIn, G, false>), grid, dim3(kBlock), 0, s, g, ns);                 \
     } while (0)
-        if (G == 4) GNN_MERGED(4, 4);
-        else if (G == 8 && few) GNN_MERGED(8, 4);
-        else if (G == 8) GNN_MERGED(8, 8);
-        else if (G == 16 && few) GNN_MERGED(16, 4);
-        else if (G == 16) GNN_MERGED(16, 8);
-        else if (few) GNN_MERGED(32, 4);
-        else GNN_MERGED(32, 8);
+        if (G == 4) GNN_MERGED(4);
+        else if (G == 8) GNN_MERGED(8);
+        else if (G == 16) GNN_MERGED(16);
+        else if (G == 32) GNN_MERGED(32);
+        else GNN_MERGED(64);
 #undef GNN_MERGED
         return;
     }

@@ -433,23 +433,30 @@ void assign_switching(int64_t n, const int64_t* rowptr, const int32_t* colidx, i
     }
 }
 
-// Entries per segment of a long row, by the entries of a partition (= of one aggregation launch of
-// the per-partition schedule).  A slot of G lanes walks a segment (or a short row of up to as many
-// entries) in dependent steps of four to eight source rows, about 0.15 us per entry, so the segment
-// length is the shortest time a launch can take: 70-100 us at 512 entries whatever the graph.  Short
-// segments cost partial sums (one row written and read per segment) and a longer combine chain, and
-// in a launch that fills the chip many times over nothing waits for a single slot.  Measured, whole
-// epochs in ms at 512 / 256 / 128 / 64 entries:
-//   GCN 64-64-16, 50 k entries per partition                1.31 / 1.03 / 0.79 / 0.66
-//   attention 100-256-256-47, 8 heads, 380 k                44.7 / 35.2 / 29.8 / 27.5
-//   GraphSAGE 100-256-256-47, 510 k (paper's order)         23.8 / 19.0 / 17.3 / 17.6
-//   GCN 128-128-128-172, directed, 810 k                    60.4 / 50.9 / 48.5 / 50.5
-//   GraphSAGE 100-256-256-47, 4.1 M                         41.8 / 41.5 / 42.2 / 43.8
-static int32_t segment_for(int64_t entries)
+// Entries per segment of a long row, by the entries of a partition (one launch of the per-partition
+// entry points) and of the graph (one launch of an epoch over the whole graph).  A slot of G lanes
+// walks a segment (or a short row of up to as many entries) in dependent steps of four to eight
+// source rows, about 0.15 us per entry, so the segment length is the shortest time a launch can
+// take: 70-100 us at 512 entries whatever the graph.  Short segments cost partial sums (one row
+// written and read per segment) and a longer combine chain, and in a launch that fills the chip many
+// times over nothing waits for a single slot.  Measured, in ms at 512 / 256 / 128 / 64 entries:
+//   partition by partition (entries of a partition)
+//     GCN 64-64-16, 50 k                                      1.31 / 1.03 / 0.79 / 0.66
+//     forward pass 128-256-256-64 by hand, 310 k              7.59 / 5.56 / 4.61 / 4.33
+//     GraphSAGE 100-256-256-47, 510 k (paper's order)         23.8 / 19.0 / 17.3 / 17.6
+//     GCN 128-128-128-172, directed, 810 k                    60.4 / 50.9 / 48.5 / 50.5
+//     GraphSAGE 100-256-256-47, 4.1 M                         41.8 / 41.5 / 42.2 / 43.8
+//   whole graph (entries of the graph)
+//     bf16 72-136-136-40, training step, 2.1 M                1.29 / 1.14 / 1.06 / 1.10
+//     attention 100-256-256-47, 8 heads, 6.2 M                10.8 / 10.6 / 10.7 / 11.1
+//     bf16 512-1024-1024-64, 6.5 M                            8.90 / 8.97 / 9.17 / 9.31
+//     GCN 128-128-128-172, directed, 52 M                     30.6 / 31.1 / 31.4 / 32.2
+//     GraphSAGE 100-256-256-47, 66 M                          37.3 / 37.9 / 38.2 / 39.4
+static int32_t segment_for(int64_t part, int64_t graph)
 {
-    if (entries < 450000) return 64;
-    if (entries < 1500000) return 128;
-    if (entries < 6000000) return 256;
+    if (part < 450000) return graph < 6000000 ? 64 : 128;
+    if (part < 1500000) return graph < 20000000 ? 128 : 256;
+    if (part < 6000000) return graph < 30000000 ? 256 : 512;
     return kSpmmSegmentMax;
 }
 
@@ -880,7 +887,7 @@ gnn_status build_host_meta(int model, int64_t n, const int64_t* rowptr, const in
 
         // ---- phase D: work items of the aggregation kernels -------------------------------------
         {
-            M.segment = segment_for(nnz / k);
+            M.segment = segment_for(nnz / k, nnz);
             std::vector<PlanPart> fw((size_t)k), bw((size_t)k);
             parallel_for(k, 1, [&](int, int64_t p) {
                 const int64_t r0 = M.off[(size_t)p], np = M.off[(size_t)p + 1] - r0;

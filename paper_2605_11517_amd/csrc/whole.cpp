@@ -211,27 +211,45 @@ void build_tables(const gnn_ctx* c, gnn_ctx* w)
     }
 }
 
+// Longest row of the merged operator that one slot sums.  A longer row's pieces are summed on their own
+// and written and read once more, a row of d floats per piece: with 64 partitions a row of 300 entries
+// is 60 pieces, and its sums are a fifth of what it fetches.  But a slot walks a row in dependent
+// steps, which must not outlast the launch.  Transposed pass + combining in ms, rows cut above
+// 64 / 128 / 256 / 512 / 1024 entries:
+//   50 k entries (GCN 64-64-16)                         0.027 / 0.036 / 0.053
+//   6.5 M entries (1024 bfloat16 columns)               2.51 / 2.45 / 2.15 / 2.11 / 2.12
+//   52 M entries, 64 partitions (128 and 172 columns)   7.74 / 6.87 / 6.13 / 5.75 / 5.69
+//   66 M entries (256 columns)                          9.64 / 8.88 / 8.63 / 8.42 / 8.23
+int64_t merged_row_max(int64_t entries, int32_t segment)
+{
+    const int64_t most = entries < 2000000 ? 64 : entries < 8000000 ? 256 : entries < 30000000 ? 512 : 1024;
+    return std::max<int64_t>(segment, most);
+}
+
 // Row pointers and work lists of a merged operator from the entries per row (device).
 void finish_rows(const gnn_ctx* c, DevMeta::Merged& m, const int32_t* cnt_dev)
 {
     const int64_t n = c->M.n;
-    const int32_t seg = c->M.segment;
     std::vector<int32_t> cnt((size_t)n);
     check(hipMemcpy(cnt.data(), cnt_dev, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
     std::vector<int64_t> rp((size_t)n + 1);
-    std::vector<int64_t> bucket((size_t)seg + 2, 0);
-    std::vector<int32_t> longs;
     rp[0] = 0;
+    for (int64_t u = 0; u < n; ++u) rp[(size_t)u + 1] = rp[(size_t)u] + (cnt[(size_t)u] & 0x7FFFFFFF);
+    // (a row with a long piece is negative here: long whatever its length)
+    const int32_t most = (int32_t)merged_row_max(rp[(size_t)n], c->M.segment);
+    std::vector<int64_t> bucket((size_t)most + 2, 0);
+    std::vector<int32_t> longs;
     for (int64_t u = 0; u < n; ++u) {
         const int32_t d = cnt[(size_t)u];
-        rp[(size_t)u + 1] = rp[(size_t)u] + d;
-        if (d > seg) longs.push_back((int32_t)u);
-        else bucket[(size_t)(seg - d) + 1]++;
+        if (d < 0 || d > most) longs.push_back((int32_t)u);
+        else bucket[(size_t)(most - d) + 1]++;
     }
     for (size_t i = 1; i < bucket.size(); ++i) bucket[i] += bucket[i - 1];
     std::vector<int32_t> rows((size_t)(n - (int64_t)longs.size()));
-    for (int64_t u = 0; u < n; ++u)
-        if (cnt[(size_t)u] <= seg) rows[(size_t)bucket[(size_t)(seg - cnt[(size_t)u])]++] = (int32_t)u;
+    for (int64_t u = 0; u < n; ++u) {
+        const int32_t d = cnt[(size_t)u];
+        if (d >= 0 && d <= most) rows[(size_t)bucket[(size_t)(most - d)]++] = (int32_t)u;
+    }
     m.entries = rp[(size_t)n];
     m.avg_len = (float)m.entries / (float)std::max<int64_t>(1, n);
     m.nrows = (int64_t)rows.size();
@@ -291,7 +309,7 @@ void build_merged(const gnn_ctx* c, DevMeta::Merged& m)
     const int64_t* toff = tmp.keep(to_device(M.toff));
     const int64_t* off = tmp.keep(to_device(M.off));
     const int64_t* boff = tmp.keep(to_device(M.boff));
-    launch_merge_count(M.toff[(size_t)M.k], M.k, toff, off, boff, c->D.bnd, c->D.trp, cnt, nullptr);
+    launch_merge_count(M.toff[(size_t)M.k], M.k, toff, off, boff, c->D.bnd, c->D.trp, cnt, c->M.segment, nullptr);
     check(hipGetLastError());
     finish_rows(c, m, cnt);
     int64_t* cursor = tmp.keep(device_array<int64_t>(n));
@@ -318,7 +336,7 @@ void build_merged_masked(const gnn_ctx* c, const DevMeta::Merged& full, DevMeta:
     const int64_t n = c->M.n;
     Temp tmp;
     int32_t* cnt = tmp.keep(device_array<int32_t>(n));
-    launch_merge_mask_count(n, full.rp, full.col, c->mask, cnt, nullptr);
+    launch_merge_mask_count(n, full.rp, full.col, c->mask, cnt, c->M.segment, nullptr);
     check(hipGetLastError());
     finish_rows(c, m, cnt);
     if (full.self_first) m.self_first = device_array<uint8_t>(n);
