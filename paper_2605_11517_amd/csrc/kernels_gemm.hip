@@ -1,172 +1,156 @@
-// Dense contractions of the path on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), gfx950.
+// Dense contractions of the path in fp32, on the bfloat16 matrix cores (v_mfma_f32_32x32x16_bf16), gfx950.
 //
 //   forward   A_p^l  = act( Z_p W^l (+ X_p W_s^l) + b^l )        [n_p x d_in] [d_in x d_out]
 //   backward  dZ_p   = dY_p (W^l)^T                              [n_p x d_out][d_out x d_in]
 //             grad W^l += Z_p^T dY_p                             reduction over the n_p rows
 //
-// One workgroup of 4 wavefronts (2 x 2) owns a BM x BN tile of C.  K is walked in steps of 16
-// through a double-buffered LDS stage.  An operand whose k index is the contiguous one in
-// memory is kept [x][k] in LDS (chunks rotated per row, see kf_chunk) and an MFMA lane fetches
-// eight k of its row with two 16-byte reads; an operand whose m (or n) index is contiguous is
-// kept [k][x], so that the 32 lanes feeding one MFMA operand column read 32 consecutive floats.
-// Widths that are not multiples of 4 floats (e.g. 47 classes) take a scalar-load variant of the
-// same kernel; tails in M, N and K are zero-filled in LDS, never in memory.
+// The fp32 matrix instruction does 64 flop per cycle and SIMD, the bfloat16 one 1024.  Every fp32
+// operand is split on its way into LDS into three bfloat16 numbers whose sum it is, exactly
+//     x = h + m + l,   h = round(x), m = round(x - h), l = x - h - m    (8 + 8 + 8 significant bits)
+// and a product is taken as the six terms
+//     l h' + m m' + h l' + m h' + h m' + h h'      (each exact in fp32, accumulated in fp32).
+// What is left out (m l' + l m' + l l') is at most 2^-25 of |x y| and has no sign of its own; the six
+// terms of 16 k are added in 6 steps where the fp32 instruction rounds 8 times.
+// What the split cannot represent - infinities, NaN, magnitudes that round up to infinity - makes
+// the element's sum a NaN or an infinity; such elements are computed again as a chain of fp32 fused
+// multiply-adds (bad elements only, see the end of the kernel).
+//
+// One workgroup of 4 wavefronts (2 x 2) owns a BM x BN tile of C.  K is walked in steps of BK
+// through a double-buffered LDS stage.  The unit of loading, splitting and LDS is eight consecutive k
+// of one row of the operand: one lane's share of an MFMA operand, 16 bytes in each of the three planes.
+// K past a segment's end is zero-filled in LDS, never in memory; rows past m or n repeat the last one
+// and are not stored.
+//
+// Bound by the splitting beside the matrix work: per stage and wavefront 24 matrix instructions of 32
+// cycles and about 150 vector instructions of 4.  Against the fp32 instruction (same tiles), ms:
+//   forward   1.2 M rows  256 x 256   1.55 -> 1.05      3 M rows  128 x 128   1.11 -> 0.86
+//   backward  1.2 M rows  256 x 256   1.56 -> 1.06      3 M rows  128 x 172   1.47 -> 1.18
+//   gradient  1.2 M rows  256 x 256   1.61 -> 1.14      3 M rows  128 x 128   1.11 -> 0.81
+// Relative error against 64 bits (normal inputs): 2.9e-7 -> 2.4e-7 (K = 256), 1.4e-7 -> 1.1e-7
+// (K = 64), gradient over 1.2 M rows 8.4e-7 -> 7.3e-7.  Magnitudes below 1e-34 lose bits: the
+// matrix cores read bfloat16 denormals (here those of m and l) as zero.
 #include "gnn_internal.h"
+#include <cfloat>
 #include <cstdlib>
 
 namespace gnnmi {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 256;
 constexpr int BK = 16;
-constexpr int PF = 1;   // stages of global loads in flight per thread; 2 and 3 measured slower, also on
-                        // the narrow (48-wide) contractions: those are bound by the MFMA work of
-                        // their padded 64-wide tile, not by loads in flight
-constexpr int SUB = 1;  // k-tiles of BK per LDS stage (one barrier per stage); 2 measured slower:
-                        // the forward contraction loses more to the larger LDS footprint than
-                        // the halved barrier count gains
-constexpr int PAD = 4;
+constexpr int GP = BK / 8;          // groups of eight k in a stage
+// Rows of a plane are 16 bytes, one group of k after the other; the pad puts the groups that the
+// lanes of a k-fast store write together into different banks (the reads are consecutive anyway).
+constexpr int PADR = 16 / GP;
 
 struct Operand {         // a matrix operand restricted to one K segment
     const float* p;
     int64_t ld;
 };
 
-// Tile whose k index is the contiguous one in memory: (slow = m or n, fast = k).
-// Thread t covers slow = t / 4 + 64 i, k = 4 (t % 4) .. + 3.
-template <int BT, bool VEC>
-__device__ inline void load_kfast(const float* __restrict__ p, int64_t ld, int64_t slow0,
-                                  int64_t nslow, int32_t k0, int32_t kend, float4 (&r)[BT / 64])
+__device__ inline uint32_t to_bf16x2(float a, float b)      // v_cvt_pk_bf16_f32: to nearest even
 {
-    const int t = threadIdx.x;
-    const int kq = (t & 3) * 4;
+    const floatx2 f = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
+// x minus one half of a pair, in one v_dot2_f32_bf16: the other half times 0 is 0, or NaN for an infinity.
+// (The pairs (-1, 0) and (0, -1) are kept from the compiler: as a literal the first becomes the inline
+// constant -1.0, which the instruction reads as the second.)
+__device__ inline float minus_half(float x, uint32_t pair, uint32_t selector)
+{
+    asm("" : "+s"(selector));
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, selector), x, false);
+}
+__device__ inline float minus_low(float x, uint32_t pair) { return minus_half(x, pair, 0x0000BF80u); }
+__device__ inline float minus_high(float x, uint32_t pair) { return minus_half(x, pair, 0xBF800000u); }
+__device__ inline void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
+{
+    h = to_bf16x2(a, b);
+    const float a1 = minus_low(a, h), b1 = minus_high(b, h);
+    m = to_bf16x2(a1, b1);
+    l = to_bf16x2(minus_low(a1, m), minus_high(b1, m));
+}
+
+// One operand's stage of BT rows x BK k: x[j] is the j-th k of this thread's group.  (BT = 64 has
+// work for half of the wavefronts, from wavefront `first` on.)  Consecutive threads take the groups of
+// a row of a k-fast operand, else consecutive rows, whose elements of one k are consecutive in memory.
+template <int BT, bool KFAST, bool VEC>
+struct Stage {
+    static constexpr int GROUPS = BT * GP;
+    static_assert(GROUPS <= kThreads, "one group per thread");
+    static constexpr int PLANE = GP * (BT + PADR);             // 16-byte units
+    float x[8];
+    const float* q;        // k-fast: this thread's group of the next stage; else: its first row of k (uniform)
+    int64_t ld;
+    int32_t row, group;
+    uint32_t col;          // else: element of that row, in bytes
+    bool on;
+
+    __device__ inline Stage(int first)
+    {
+        const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) - (GROUPS < kThreads ? first : 0);
+        const int t = 64 * w + (int)(threadIdx.x & 63);
+        on = GROUPS == kThreads || (w >= 0 && w < GROUPS / 64);
+        row = KFAST ? t / GP : t % BT;
+        group = KFAST ? t % GP : 64 * w / BT;
+    }
+    // rows past the end read the last one
+    __device__ inline void begin(const Operand& o, int64_t row0, int64_t nrows, int64_t k0)
+    {
+        const int64_t r = row0 + row < nrows ? row0 + row : nrows - 1;
+        ld = o.ld;
+        q = o.p + (KFAST ? r * ld + k0 + 8 * group : (k0 + 8 * group) * ld);
+        col = 4u * (uint32_t)r;
+    }
+    __device__ inline float at(int32_t j) const
+    {
+        return KFAST ? q[j] : *reinterpret_cast<const float*>(reinterpret_cast<const char*>(q + j * ld) + col);
+    }
+    __device__ inline void advance() { q += KFAST ? BK : BK * ld; }
+    // `left`: k of the segment from this stage on.  Loads past its end are clamped to its last k.
+    __device__ inline void load(int32_t left)
+    {
+        if (GROUPS < kThreads && !on) return;
+        const int32_t mine = left - 8 * group;
+        if (KFAST && VEC) {
+            const float4 a = *reinterpret_cast<const float4*>(q + (mine >= 4 ? 0 : mine - 4));
+            const float4 b = *reinterpret_cast<const float4*>(q + (mine >= 8 ? 4 : mine - 4));
+            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+            x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+        } else {
 #pragma unroll
-    for (int i = 0; i < BT / 64; ++i) {
-        const int64_t sidx = slow0 + (t >> 2) + 64 * i;
-        const int32_t k = k0 + kq;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (VEC) {
-            // unconditional load from a clamped (always valid) address, zeroed afterwards:
-            // without branches the compiler can keep several tiles of loads in flight
-            const float* q = p + (sidx < nslow ? sidx : nslow - 1) * ld + (k < kend ? k : k0);
-            const float4 x = *reinterpret_cast<const float4*>(q);
-            v = x;   // rows / k past the end are zeroed when the tile goes to LDS
-        } else if (sidx < nslow) {
-            const float* q = p + sidx * ld + k;
-            {
-                if (k + 0 < kend) v.x = q[0];
-                if (k + 1 < kend) v.y = q[1];
-                if (k + 2 < kend) v.z = q[2];
-                if (k + 3 < kend) v.w = q[3];
-            }
+            for (int j = 0; j < 8; ++j) x[j] = at(j < mine ? j : mine - 1);
         }
-        r[i] = v;
     }
-}
-// k-fast tiles are kept [x][k] in LDS: one 16-byte store per register, and an MFMA lane later
-// fetches eight consecutive k of its row with two 16-byte reads.  Rows are BK floats apart and
-// the four 16-byte chunks of row x are rotated by x / 4: sixteen consecutive lanes then touch
-// all 64 banks exactly once both when storing (4 rows x 4 chunks) and when reading (16 rows,
-// one chunk each); a padded row stride can satisfy only one of the two.
-constexpr int KF_LD = BK;
-__device__ inline int kf_chunk(int x, int chunk) { return 4 * ((chunk + (x >> 2)) & 3); }
-template <int BT>
-__device__ inline void store_kfast(float* S, const float4 (&r)[BT / 64])
-{
-    const int t = threadIdx.x;
+    // flip: the sign bit, or 0.  Of the k past the segment's end one operand (ZERO) is zeroed: the other
+    // repeats an element of the same row, which, were it infinite, has made the row's sums so already.
+    template <bool ZERO>
+    __device__ inline void store(uint4* S, int32_t left, uint32_t flip)
+    {
+        if (GROUPS < kThreads && !on) return;
+        if (ZERO) {
+            const int32_t mine = left - 8 * group;
 #pragma unroll
-    for (int i = 0; i < BT / 64; ++i) {
-        const int x = (t >> 2) + 64 * i;
-        *reinterpret_cast<float4*>(S + x * KF_LD + kf_chunk(x, t & 3)) = r[i];
-    }
-}
-
-// Tile whose m (or n) index is the contiguous one: (slow = k, fast = m or n).
-// Thread t covers k = t / (BT/4) + (1024/BT) i, fast = 4 (t % (BT/4)) .. + 3.
-template <int BT, bool VEC>
-__device__ inline void load_kslow(const float* __restrict__ p, int64_t ld, int64_t k0, int64_t kend,
-                                  int64_t fast0, int64_t nfast, float4 (&r)[BT / 64])
-{
-    constexpr int TPR = BT / 4;           // threads per k row
-    constexpr int KPP = kThreads / TPR;   // k rows per pass
-    const int t = threadIdx.x;
-    const int fq = (t % TPR) * 4;
-#pragma unroll
-    for (int i = 0; i < BT / 64; ++i) {
-        const int64_t k = k0 + t / TPR + KPP * i;
-        const int64_t f = fast0 + fq;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (VEC) {
-            const float* q = p + (k < kend ? k : k0) * ld + (f < nfast ? f : fast0);
-            const float4 x = *reinterpret_cast<const float4*>(q);
-            v = x;   // rows / k past the end are zeroed when the tile goes to LDS
-        } else if (k < kend) {
-            const float* q = p + k * ld + f;
-            {
-                if (f + 0 < nfast) v.x = q[0];
-                if (f + 1 < nfast) v.y = q[1];
-                if (f + 2 < nfast) v.z = q[2];
-                if (f + 3 < nfast) v.w = q[3];
-            }
+            for (int j = 0; j < 8; ++j) x[j] = (KFAST && VEC ? (j & 4) : j) < mine ? x[j] : 0.f;
         }
-        r[i] = v;
+        uint32_t h[4], m[4], l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float a = __uint_as_float(__float_as_uint(x[2 * j]) ^ flip);
+            const float b = __uint_as_float(__float_as_uint(x[2 * j + 1]) ^ flip);
+            split2(a, b, h[j], m[j], l[j]);
+        }
+        uint4* d = S + group * (BT + PADR) + row;
+        d[0] = make_uint4(h[0], h[1], h[2], h[3]);
+        d[PLANE] = make_uint4(m[0], m[1], m[2], m[3]);
+        d[2 * PLANE] = make_uint4(l[0], l[1], l[2], l[3]);
     }
-}
-template <int BT>
-__device__ inline void store_kslow(float* S, const float4 (&r)[BT / 64])
-{
-    constexpr int TPR = BT / 4;
-    constexpr int KPP = kThreads / TPR;
-    const int t = threadIdx.x;
-    const int fq = (t % TPR) * 4;
-#pragma unroll
-    for (int i = 0; i < BT / 64; ++i)
-        *reinterpret_cast<float4*>(S + (t / TPR + KPP * i) * (BT + PAD) + fq) = r[i];
-}
-
-// Fragment of one operand for a whole BK = 16 tile: f[j] is the value this lane feeds to the
-// j-th MFMA k-step.  The two half-waves of a 32x32x2 MFMA supply k = 0 and k = 1 of a step;
-// here half h supplies k = 8 h + j of the tile at step j (the k order inside a tile is free
-// as long as A and B agree), which makes a k-fast row fragment eight consecutive floats.
-template <int BT, bool KFAST>
-__device__ inline void load_fragment(const float* S, int x, int half, float (&f)[8])
-{
-    if (KFAST) {
-        const float4 lo = *reinterpret_cast<const float4*>(S + x * KF_LD + kf_chunk(x, 2 * half));
-        const float4 hi = *reinterpret_cast<const float4*>(S + x * KF_LD + kf_chunk(x, 2 * half + 1));
-        f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
-        f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = S[(8 * half + j) * (BT + PAD) + x];
-    }
-}
-
-// Zero the vectors of a tile that lie past the end of the matrix (their loads were clamped to
-// valid addresses).  Done when the registers are written to LDS, not at load time, so that the
-// loads of several tiles stay in flight.
-template <int BT>
-__device__ inline void mask_kfast(int64_t slow0, int64_t nslow, int64_t k0, int64_t kend, float4 (&r)[BT / 64])
-{
-    const int t = threadIdx.x;
-    const int64_t k = k0 + (t & 3) * 4;
-#pragma unroll
-    for (int i = 0; i < BT / 64; ++i)
-        if (!(slow0 + (t >> 2) + 64 * i < nslow && k < kend)) r[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-template <int BT>
-__device__ inline void mask_kslow(int64_t k0, int64_t kend, int64_t fast0, int64_t nfast, float4 (&r)[BT / 64])
-{
-    constexpr int TPR = BT / 4;
-    constexpr int KPP = kThreads / TPR;
-    const int t = threadIdx.x;
-    const int64_t f = fast0 + (t % TPR) * 4;
-#pragma unroll
-    for (int i = 0; i < BT / 64; ++i)
-        if (!(k0 + t / TPR + KPP * i < kend && f < nfast)) r[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
+};
 
 struct GemmArgs {
     Operand a[2], b[2];      // up to two K segments
@@ -198,15 +182,16 @@ __device__ inline bool tile_of_block(int64_t b, int64_t mt, int32_t nt, int64_t&
 
 // A_KFAST: A(m,k) = a[m*lda + k]   (else a[k*lda + m])
 // B_KFAST: B(k,n) = b[n*ldb + k]   (else b[k*ldb + n])
+// An element of C is the same sum in the same order whatever the tile.
 template <int BM, int BN, bool A_KFAST, bool B_KFAST, bool VEC_A, bool VEC_B>
-__global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
+__global__ __launch_bounds__(kThreads, 3) void k_gemm(const GemmArgs g)
 {
     constexpr int WM = BM / 2, WN = BN / 2;   // wave tile
     constexpr int TM = WM / 32, TN = WN / 32; // 32x32 MFMA tiles per wave
-    constexpr int A_TILE = A_KFAST ? BM * KF_LD : BK * (BM + PAD);
-    constexpr int B_TILE = B_KFAST ? BN * KF_LD : BK * (BN + PAD);
-    __shared__ __attribute__((aligned(16))) float As[2][SUB * A_TILE];
-    __shared__ __attribute__((aligned(16))) float Bs[2][SUB * B_TILE];
+    using StageA = Stage<BM, A_KFAST, VEC_A>;
+    using StageB = Stage<BN, B_KFAST, VEC_B>;
+    __shared__ __attribute__((aligned(16))) uint4 As[2][3 * StageA::PLANE];
+    __shared__ __attribute__((aligned(16))) uint4 Bs[2][3 * StageB::PLANE];
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -229,11 +214,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
         }
         cbase += (int64_t)blockIdx.z * g.split_stride;
     }
-    // a stage is SUB consecutive k-tiles of one segment (tiles past the segment's end are zero)
-    constexpr int SK = BK * SUB;
-    const int64_t tiles0 = kend0 > kbeg ? (kend0 - kbeg + SK - 1) / SK : 0;
-    const int64_t tiles1 = (g.kseg[1] + SK - 1) / SK;
-    const int64_t ntiles = tiles0 + tiles1;
+    const int32_t tiles0 = kend0 > kbeg ? (int32_t)((kend0 - kbeg + BK - 1) / BK) : 0;
+    const int32_t ntiles = tiles0 + (g.kseg[1] + BK - 1) / BK;
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -243,87 +225,107 @@ __global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // Register ring of PF tiles: the global loads of tile t + PF are issued while tile t is
-    // multiplied, so that a load has PF tile-times to arrive (one tile-time is far shorter than
-    // the memory latency, above all with the fast bf16 MFMA).
-    float4 ra[PF][SUB][BM / 64], rb[PF][SUB][BN / 64];
-    auto load_tile = [&](int64_t t, float4 (&ra)[SUB][BM / 64], float4 (&rb)[SUB][BN / 64]) {
-        const int seg = t < tiles0 ? 0 : 1;
-        const int64_t ks = seg == 0 ? kbeg + t * SK : (t - tiles0) * SK;
-        const int64_t kend = seg == 0 ? kend0 : (int64_t)g.kseg[1];
-#pragma unroll
-        for (int u = 0; u < SUB; ++u) {
-            // a tile wholly past the end is fetched from the segment's first tile and zeroed later
-            const int64_t k0 = ks + u * BK < kend ? ks + u * BK : ks;
-            if (A_KFAST) load_kfast<BM, VEC_A>(g.a[seg].p, g.a[seg].ld, m0, g.m, (int32_t)k0, (int32_t)kend, ra[u]);
-            else load_kslow<BM, VEC_A>(g.a[seg].p, g.a[seg].ld, k0, kend, m0, g.m, ra[u]);
-            if (B_KFAST) load_kfast<BN, VEC_B>(g.b[seg].p, g.b[seg].ld, n0, g.n, (int32_t)k0, (int32_t)kend, rb[u]);
-            else load_kslow<BN, VEC_B>(g.b[seg].p, g.b[seg].ld, k0, kend, n0, g.n, rb[u]);
-        }
+    StageA sa(0);
+    StageB sb(BM == 64 ? 2 : 0);
+    int32_t left = 0;                  // k of the segment from the stage that is loaded next
+    auto begin = [&](int seg) {
+        const int64_t k0 = seg == 0 ? kbeg : 0;
+        left = (int32_t)((seg == 0 ? kend0 : (int64_t)g.kseg[1]) - k0);
+        sa.begin(g.a[seg], m0, g.m, k0);
+        sb.begin(g.b[seg], n0, g.n, k0);
     };
-    auto store_tile = [&](int buf, int64_t t, const float4 (&ra_in)[SUB][BM / 64],
-                          const float4 (&rb_in)[SUB][BN / 64]) {
-        const int seg = t < tiles0 ? 0 : 1;
-        const int64_t ks = seg == 0 ? kbeg + t * SK : (t - tiles0) * SK;
-        const int64_t kend = seg == 0 ? kend0 : (int64_t)g.kseg[1];
+    // The matrix cores round sums down, not to nearest: a bias of half a unit per step, which the many
+    // partial sums of a weight gradient would add up (gradient over 1.2 M rows: relative error 2.7e-6
+    // instead of 8e-7).  So A, and the sums with it, changes its sign for the second and third quarter
+    // of the stages: + - - +, in which a bias that grows with the sums cancels.
+    const int32_t turn0 = ntiles / 4, turn1 = turn0 + ntiles / 2;       // (the last stage is a positive one)
+    auto negative = [&](int32_t t) { return t >= turn0 && t < turn1; };
+    auto store = [&](int32_t t) {
+        sa.template store<false>(As[t & 1], left, negative(t) ? 0x80000000u : 0u);
+        sb.template store<true>(Bs[t & 1], left, 0u);
+        sa.advance();
+        sb.advance();
+        left -= BK;
+    };
+    const int half = lane >> 5, xl = lane & 31;
+    auto multiply = [&](int32_t t) {
+        const uint4* ap = As[t & 1] + half * (BM + PADR) + wm0 + xl;
+        const uint4* bp = Bs[t & 1] + half * (BN + PADR) + wn0 + xl;
+        bf16x8 av[3][TM], bv[3][TN];
 #pragma unroll
-        for (int u = 0; u < SUB; ++u) {
-            const bool live = ks + u * BK < kend;
-            const int64_t k0 = live ? ks + u * BK : ks;
-            const int64_t ke = live ? kend : ks;        // an empty range zeroes the whole tile
-            float4 ra[BM / 64], rb[BN / 64];
+        for (int p = 0; p < 3; ++p) {
 #pragma unroll
-            for (int i = 0; i < BM / 64; ++i) ra[i] = ra_in[u][i];
+            for (int i = 0; i < TM; ++i) av[p][i] = __builtin_bit_cast(bf16x8, ap[p * StageA::PLANE + 32 * i]);
 #pragma unroll
-            for (int i = 0; i < BN / 64; ++i) rb[i] = rb_in[u][i];
-            if (A_KFAST) { mask_kfast<BM>(m0, g.m, k0, ke, ra); store_kfast<BM>(As[buf] + u * A_TILE, ra); }
-            else { mask_kslow<BM>(k0, ke, m0, g.m, ra); store_kslow<BM>(As[buf] + u * A_TILE, ra); }
-            if (B_KFAST) { mask_kfast<BN>(n0, g.n, k0, ke, rb); store_kfast<BN>(Bs[buf] + u * B_TILE, rb); }
-            else { mask_kslow<BN>(k0, ke, n0, g.n, rb); store_kslow<BN>(Bs[buf] + u * B_TILE, rb); }
+            for (int j = 0; j < TN; ++j) bv[p][j] = __builtin_bit_cast(bf16x8, bp[p * StageB::PLANE + 32 * j]);
         }
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};   // small terms first
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[PA[q]][i], bv[PB[q]][j], acc[i][j], 0, 0, 0);
+    };
+    auto negate = [&] {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = -acc[i][j][r];
     };
 
-#pragma unroll
-    for (int d = 0; d < PF; ++d)
-        if (ntiles > 0) load_tile(d < ntiles ? d : ntiles - 1, ra[d], rb[d]);
-    if (ntiles > 0) store_tile(0, 0, ra[0], rb[0]);
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < ntiles; t0 += PF) {
-#pragma unroll
-        for (int dd = 0; dd < PF; ++dd) {
-            const int64_t t = t0 + dd;
-            if (t >= ntiles) break;
-            const int buf = (int)(t & 1);
-            // slot dd held stage t, already in LDS; past the end the last stage is fetched again
-            // (never used) so that the load stream has no branches
-            load_tile(t + PF < ntiles ? t + PF : ntiles - 1, ra[dd], rb[dd]);
+    if (ntiles > 0) {
+        begin(tiles0 > 0 ? 0 : 1);
+        sa.load(left);
+        sb.load(left);
+        store(0);
+        __syncthreads();
+        for (int32_t t = 0; t + 1 < ntiles; ++t) {
+            if (negative(t) != negative(t - 1)) negate();
+            if (t + 1 == tiles0) begin(1);
+            sa.load(left);
+            sb.load(left);
             // keep the loads where they are: left alone, the scheduler sinks them below the
             // MFMA block, right in front of the wait that precedes the LDS store
             __builtin_amdgcn_sched_barrier(0);
-            const int half = lane >> 5, xl = lane & 31;
-#pragma unroll
-            for (int u = 0; u < SUB; ++u) {
-                float af[TM][8], bf[TN][8];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    load_fragment<BM, A_KFAST>(As[buf] + u * A_TILE, wm0 + 32 * i + xl, half, af[i]);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    load_fragment<BN, B_KFAST>(Bs[buf] + u * B_TILE, wn0 + 32 * j + xl, half, bf[j]);
-#pragma unroll
-                for (int st = 0; st < 8; ++st)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][st], bf[j][st], acc[i][j], 0, 0, 0);
-            }
-            if (t + 1 < ntiles) store_tile(buf ^ 1, t + 1, ra[(dd + 1) % PF], rb[(dd + 1) % PF]);
+            multiply(t);
+            store(t + 1);
             __syncthreads();
         }
+        if (negative(ntiles - 2)) negate();
+        multiply(ntiles - 1);
+    }
+
+    // elements whose sum is no finite number (0 times it is NaN)
+    uint64_t bad = 0;
+    float zero = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) zero = fmaf(acc[i][j][r], 0.f, zero);
+    if (zero != 0.f) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (!(fabsf(acc[i][j][r]) <= FLT_MAX)) bad |= 1ull << ((i * TN + j) * 16 + r);
     }
 
     // epilogue: lane holds C[8 (r/4) + 4 (lane/32) + r%4][lane%32] of each 32x32 tile
+    const bool plain = !g.relu && !g.accumulate;
+    auto put = [&](float* dst, float v) {
+        if (g.relu) v = v > 0.f ? v : 0.f;
+        if (g.accumulate) v += *dst;
+        *dst = v;
+    };
+    const bool inside = m0 + BM <= g.m && __builtin_amdgcn_ballot_w64(bad != 0) == 0;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -331,17 +333,39 @@ __global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g)
             const int32_t col = n0 + wn0 + 32 * j + (lane & 31);
             if (col >= g.n) continue;
             const float bv = g.bias ? g.bias[col] : 0.f;
+            const int64_t row0 = m0 + wm0 + 32 * i + 4 * (lane >> 5);
+            float* dst = cbase + row0 * g.ldc + col;
+            if (inside && plain) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (row >= g.m) continue;
-                float v = acc[i][j][r] + bv;
-                if (g.relu) v = v > 0.f ? v : 0.f;
-                float* dst = cbase + row * g.ldc + col;
-                if (g.accumulate) v += *dst;
-                *dst = v;
+                for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * g.ldc] = acc[i][j][r] + bv;
+            } else if (inside) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) put(dst + (8 * (r >> 2) + (r & 3)) * g.ldc, acc[i][j][r] + bv);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t o = 8 * (r >> 2) + (r & 3);
+                    if (row0 + o < g.m && !((bad >> ((i * TN + j) * 16 + r)) & 1)) put(dst + o * g.ldc, acc[i][j][r] + bv);
+                }
             }
         }
+    while (bad) {
+        const int e = __ffsll((unsigned long long)bad) - 1;
+        bad &= bad - 1;
+        const int r = e & 15, j = (e >> 4) % TN, i = (e >> 4) / TN;
+        const int32_t col = n0 + wn0 + 32 * j + (lane & 31);
+        const int64_t row = m0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (col >= g.n || row >= g.m) continue;
+        float v = 0.f;
+        for (int seg = 0; seg < 2; ++seg) {
+            const int64_t ke = seg == 0 ? kend0 : (int64_t)g.kseg[1];
+            const Operand a = g.a[seg], b = g.b[seg];
+            for (int64_t k = seg == 0 ? kbeg : 0; k < ke; ++k)
+                v = fmaf(A_KFAST ? a.p[row * a.ld + k] : a.p[k * a.ld + row],
+                         B_KFAST ? b.p[col * b.ld + k] : b.p[k * b.ld + col], v);
+        }
+        put(cbase + row * g.ldc + col, v + (g.bias ? g.bias[col] : 0.f));
+    }
 }
 
 // c[i] += sum_s partial[s * stride + i].  A block covers 64 groups of four consecutive
@@ -436,17 +460,14 @@ template <bool A_KFAST, bool B_KFAST>
 void launch_gemm(const GemmArgs& g, int splits, hipStream_t s)
 {
     if (g.m <= 0 || g.n <= 0) return;
-    // float4 loads need 16-byte aligned rows, and the contiguous index of the operand (k for a
-    // k-fast operand, m or n otherwise) must consist of whole float4s; decided per operand
-    bool va = true, vb = true;
+    // 16-byte loads along k need aligned rows and whole vectors; decided per operand (operands whose m
+    // or n index is the contiguous one are read element by element, consecutive lanes side by side)
+    bool va = A_KFAST, vb = B_KFAST;
     for (int i = 0; i < 2; ++i) {
         if (g.kseg[i] == 0) continue;
-        va = va && aligned16(g.a[i].p) && g.a[i].ld % 4 == 0 && (!A_KFAST || g.kseg[i] % 4 == 0);
-        vb = vb && aligned16(g.b[i].p) && g.b[i].ld % 4 == 0 && (!B_KFAST || g.kseg[i] % 4 == 0);
+        va = va && aligned16(g.a[i].p) && g.a[i].ld % 4 == 0 && g.kseg[i] % 4 == 0;
+        vb = vb && aligned16(g.b[i].p) && g.b[i].ld % 4 == 0 && g.kseg[i] % 4 == 0;
     }
-    // (an operand whose m or n index is the contiguous one needs no such condition: its rows are
-    // ld >= m (or n) floats long with ld a multiple of 4, so the last vector of a row stays inside
-    // the row; what it reads past m (or n) only reaches columns of C that are never stored)
     const bool big_m = g.m > 64, big_n = g.n > 64;
     static const bool xcd_map = [] {
         const char* e = getenv("GNNMI_GEMM_XCD_MAP");
@@ -467,24 +488,32 @@ void launch_gemm(const GemmArgs& g, int splits, hipStream_t s)
         }                                                                                       \
     } while (0)
     // the last 128-wide column tile would be less than half used: 64-wide tiles waste less
-    // (172 columns: 192 computed instead of 256, 0.55 -> 0.42 ms on 780 k rows)
+    // (172 columns: 192 computed instead of 256, 0.57 -> 0.55 ms on 1.2 M rows, K = 128)
     const bool tail64 = splits == 1 && (g.n + 63) / 64 * 64 < (g.n + 127) / 128 * 128;
-    // short K: the product is bound by its loads and stores, 64-row tiles keep more workgroups
-    // per CU in flight (+5 % at K = 128)
-    const bool small_k = splits == 1 && g.kseg[0] + g.kseg[1] <= 128;
+    // 64 x 64 tiles where all of them are resident at once, five to a CU: tiles of 128 x 128 would leave
+    // CUs idle or alone with the latency of a stage (256 columns, K = 256, 64 / 128: 3,000 rows 16 / 27 us,
+    // 15,600 rows 28 / 31 us, 40,000 rows - 2,504 tiles - 58 / 48 us)
+    const bool few = ((g.m + 63) / 64) * ((g.n + 63) / 64) * splits <= 5 * 256;
 #define GNN_GEMM_TILE(VA, VB)                                     \
     do {                                                          \
-        if (big_m && big_n && tail64) GNN_GEMM(128, 64, VA, VB);  \
-        else if (small_k && big_n) GNN_GEMM(64, 128, VA, VB);     \
+        if (few) GNN_GEMM(64, 64, VA, VB);                        \
+        else if (big_m && big_n && tail64) GNN_GEMM(128, 64, VA, VB); \
         else if (big_m && big_n) GNN_GEMM(128, 128, VA, VB);      \
         else if (big_m) GNN_GEMM(128, 64, VA, VB);                \
         else if (big_n) GNN_GEMM(64, 128, VA, VB);                \
         else GNN_GEMM(64, 64, VA, VB);                            \
     } while (0)
-    if (va && vb) GNN_GEMM_TILE(true, true);
-    else if (va) GNN_GEMM_TILE(true, false);
-    else if (vb) GNN_GEMM_TILE(false, true);
-    else GNN_GEMM_TILE(false, false);
+    if constexpr (A_KFAST && B_KFAST) {
+        if (va && vb) GNN_GEMM_TILE(true, true);
+        else if (va) GNN_GEMM_TILE(true, false);
+        else if (vb) GNN_GEMM_TILE(false, true);
+        else GNN_GEMM_TILE(false, false);
+    } else if constexpr (A_KFAST) {
+        if (va) GNN_GEMM_TILE(true, false);
+        else GNN_GEMM_TILE(false, false);
+    } else {
+        GNN_GEMM_TILE(false, false);
+    }
 #undef GNN_GEMM_TILE
 #undef GNN_GEMM
 }
