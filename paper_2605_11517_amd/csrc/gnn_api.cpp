@@ -467,13 +467,20 @@ void collect_profile(gnn_ctx* c)
 void zero_weight_grads(gnn_ctx* c, hipStream_t s)
 {
     Timed t(c, s, GNN_K_OTHER);
+    FloatArray arrays[16];
+    int count = 0;
+    auto zero = [&](void* p, int64_t floats) {
+        arrays[count++] = {(float*)p, floats};
+        if (count == 16) launch_fill_zero(arrays, count, s), count = 0;
+    };
     for (int32_t l = 0; l < c->L; ++l) {
-        const int64_t wsz = (int64_t)c->dims[(size_t)l] * c->dims[(size_t)l + 1] * 4;
-        launch_fill_zero(c->gw[(size_t)3 * l], wsz, s);
-        if (c->model == GNN_SAGE_MEAN) launch_fill_zero(c->gw[(size_t)3 * l + 1], wsz, s);
-        if (c->model == GNN_GAT) launch_fill_zero(c->gw[(size_t)3 * l + 1], (int64_t)2 * c->dims[(size_t)l + 1] * 4, s);
-        if (c->has_bias) launch_fill_zero(c->gw[(size_t)3 * l + 2], (int64_t)c->dims[(size_t)l + 1] * 4, s);
+        const int64_t dout = c->dims[(size_t)l + 1], weights = c->dims[(size_t)l] * dout;
+        zero(c->gw[(size_t)3 * l], weights);
+        if (c->model == GNN_SAGE_MEAN) zero(c->gw[(size_t)3 * l + 1], weights);
+        if (c->model == GNN_GAT) zero(c->gw[(size_t)3 * l + 1], 2 * dout);
+        if (c->has_bias) zero(c->gw[(size_t)3 * l + 2], dout);
     }
+    launch_fill_zero(arrays, count, s);
 }
 
 static inline uint64_t splitmix64(uint64_t x)
@@ -850,11 +857,17 @@ void xf_aggregate_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, 
                 GemmSeg seg;
                 seg.a = (const float*)in_own; seg.lda = din;
                 seg.b = ws.p; seg.ldb = ws.ld; seg.k = din;
+                // the aggregate is added and the activation taken where the product is stored (a pass of
+                // its own read both again: 0.67 ms on 1.2 M rows of 256, beside a product of 1.1 ms)
+                ep.add = Z; ep.ldadd = dp;
+                ep.relu = relu;
                 launch_gemm_nn(&seg, 1, out, dout, np, dout, ep, s);
             }
         }
-        Timed t(c, s, GNN_K_OTHER);
-        launch_add_padded(out, Z, np, dout, dp, nullptr, 1, relu, s);
+        if (b16) {
+            Timed t(c, s, GNN_K_OTHER);
+            launch_add_padded(out, Z, np, dout, dp, nullptr, 1, relu, s);
+        }
     } else if (b16 && layer < c->L) {
         // hidden layer with bfloat16 storage: the output rows are rounded once, here
         Timed t(c, s, GNN_K_OTHER);

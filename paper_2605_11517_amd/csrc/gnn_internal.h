@@ -264,6 +264,8 @@ struct GemmEpilogue {
     const float* bias = nullptr;      // per column, may be null
     int relu = 0;
     int accumulate = 0;               // C += result instead of C = result
+    const float* add = nullptr;       // matrix added to the result before the activation (rows ldadd floats
+    int64_t ldadd = 0;                // apart), may be null; fp32 products only
 };
 // C[M x N] = sum over segments A[m, k] (row-major, lda) * B[k, n] (row-major, ldb)
 void launch_gemm_nn(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64_t m, int32_t n,
@@ -403,6 +405,12 @@ hipError_t launch_loss_static(const float* logits, const int32_t* labels, const 
                               hipStream_t s);
 
 void launch_fill_zero(void* p, int64_t bytes, hipStream_t s);
+// the same for several arrays (sizes in whole floats) in one launch, sixteen at a time
+struct FloatArray {
+    float* p;
+    int64_t count;
+};
+void launch_fill_zero(const FloatArray* arrays, int count, hipStream_t s);
 // gcol[e] = lcol[e] < n_own ? base + lcol[e] : bnd[lcol[e] - n_own] for e in [0, count)
 void launch_global_columns(const int32_t* lcol, int32_t* gcol, int64_t count, int64_t n_own, int64_t base,
                            const int32_t* bnd, hipStream_t s);

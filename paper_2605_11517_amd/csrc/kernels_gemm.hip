@@ -162,6 +162,8 @@ struct GemmArgs {
     const float* bias;
     int32_t relu;
     int32_t accumulate;
+    const float* add;        // added before the activation, may be null
+    int64_t ldadd;
     int64_t split_chunk;     // K per split (multiple of BK); 0 = no split
     int64_t split_stride;    // elements between the partial C of consecutive splits
     const int2* splits;      // K range of every split (null: split_chunk apart)
@@ -319,8 +321,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_gemm(const GemmArgs g)
     }
 
     // epilogue: lane holds C[8 (r/4) + 4 (lane/32) + r%4][lane%32] of each 32x32 tile
-    const bool plain = !g.relu && !g.accumulate;
-    auto put = [&](float* dst, float v) {
+    const bool plain = !g.relu && !g.accumulate && !g.add;
+    auto put = [&](int64_t row, int32_t col, float v) {
+        float* dst = cbase + row * g.ldc + col;
+        if (g.add) v += g.add[row * g.ldadd + col];
         if (g.relu) v = v > 0.f ? v : 0.f;
         if (g.accumulate) v += *dst;
         *dst = v;
@@ -340,12 +344,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_gemm(const GemmArgs g)
                 for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * g.ldc] = acc[i][j][r] + bv;
             } else if (inside) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) put(dst + (8 * (r >> 2) + (r & 3)) * g.ldc, acc[i][j][r] + bv);
+                for (int r = 0; r < 16; ++r) put(row0 + 8 * (r >> 2) + (r & 3), col, acc[i][j][r] + bv);
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int64_t o = 8 * (r >> 2) + (r & 3);
-                    if (row0 + o < g.m && !((bad >> ((i * TN + j) * 16 + r)) & 1)) put(dst + o * g.ldc, acc[i][j][r] + bv);
+                    if (row0 + o < g.m && !((bad >> ((i * TN + j) * 16 + r)) & 1)) put(row0 + o, col, acc[i][j][r] + bv);
                 }
             }
         }
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_gemm(const GemmArgs g)
                 v = fmaf(A_KFAST ? a.p[row * a.ld + k] : a.p[k * a.ld + row],
                          B_KFAST ? b.p[col * b.ld + k] : b.p[k * b.ld + col], v);
         }
-        put(cbase + row * g.ldc + col, v + (g.bias ? g.bias[col] : 0.f));
+        put(row, col, v + (g.bias ? g.bias[col] : 0.f));
     }
 }
 
@@ -537,6 +541,7 @@ void launch_gemm_nn(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64_
     }
     g.c = c; g.ldc = ldc; g.m = m; g.n = n;
     g.bias = ep.bias; g.relu = ep.relu; g.accumulate = ep.accumulate;
+    g.add = ep.add; g.ldadd = ep.ldadd;
     launch_gemm<true, false>(g, 1, s);
 }
 
@@ -550,6 +555,7 @@ void launch_gemm_nt(const float* a, int64_t lda, const float* b, int64_t ldb, fl
     g.kseg[0] = k; g.kseg[1] = 0;
     g.c = c; g.ldc = ldc; g.m = m; g.n = n;
     g.bias = ep.bias; g.relu = ep.relu; g.accumulate = ep.accumulate;
+    g.add = ep.add; g.ldadd = ep.ldadd;
     launch_gemm<true, true>(g, 1, s);
 }
 
@@ -565,6 +571,7 @@ void launch_gemm_nt2(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64
     }
     g.c = c; g.ldc = ldc; g.m = m; g.n = n;
     g.bias = ep.bias; g.relu = ep.relu; g.accumulate = ep.accumulate;
+    g.add = ep.add; g.ldadd = ep.ldadd;
     launch_gemm<true, true>(g, 1, s);
 }
 

@@ -1276,6 +1276,17 @@ __global__ __launch_bounds__(kBlock) void k_global_columns(const int32_t* __rest
     }
 }
 
+// Several small arrays at once: the gradients of three layers are nine launches of 2 us, with gaps
+// of 5 us between them, before anything else of an epoch runs.
+struct FloatArrays {
+    static constexpr int kMost = 16;
+    FloatArray a[kMost];
+};
+__global__ __launch_bounds__(kBlock) void k_fill_zero_arrays(const FloatArrays f)
+{
+    const FloatArray a = f.a[blockIdx.y];
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < a.count; i += (int64_t)gridDim.x * kBlock) a.p[i] = 0.f;
+}
 __global__ __launch_bounds__(kBlock) void k_fill_zero(uint4* __restrict__ p, int64_t n16,
                                                       uint8_t* __restrict__ tail, int ntail)
 {
@@ -1733,6 +1744,22 @@ void launch_fill_zero(void* p, int64_t bytes, hipStream_t s)
     blocks = blocks < 1 ? 1 : (blocks > 16384 ? 16384 : blocks);
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(kBlock), 0, s, (uint4*)p, n16,
                        (uint8_t*)p + n16 * 16, ntail);
+}
+
+void launch_fill_zero(const FloatArray* arrays, int count, hipStream_t s)
+{
+    for (int a0 = 0; a0 < count; a0 += FloatArrays::kMost) {
+        FloatArrays f{};
+        int64_t most = 0;
+        const int n = std::min(count - a0, (int)FloatArrays::kMost);
+        for (int a = 0; a < n; ++a) {
+            f.a[a] = arrays[a0 + a];
+            most = std::max(most, f.a[a].count);
+        }
+        if (most <= 0) continue;
+        const int64_t blocks = std::min<int64_t>((most + 4 * kBlock - 1) / (4 * kBlock), 1024);
+        hipLaunchKernelGGL(k_fill_zero_arrays, dim3((unsigned)blocks, (unsigned)n), dim3(kBlock), 0, s, f);
+    }
 }
 
 }  // namespace gnnmi
