@@ -214,9 +214,11 @@ __device__ inline void block_rows(const int2* __restrict__ blk, int64_t rows, in
 }
 
 // dy = scale * g * [act > 0] (act == null: dy aliases g, nothing is written) and per-block column
-// sums of dy into partial[block][d].  A block covers 256 rows.  Up to 256 columns are handled at
-// a time: the block's threads form 256 / width row groups that walk the rows together (four
-// rows in flight per thread), and the groups are combined through LDS in a fixed order.
+// sums of dy into partial[block][d].  A block covers 256 rows of kActColumns columns: the block's
+// threads form row groups that walk the rows together (four rows in flight per thread), and the groups
+// are combined through LDS in a fixed order.  (Blocks of 256 rows and all columns: 15 blocks on 3,000
+// rows of 256, each a chain of 16 loads, 32 us.)
+constexpr int kActColumns = 64;
 __global__ __launch_bounds__(kBlock) void k_act_bwd(const float* __restrict__ g,
                                                     const float* __restrict__ act,
                                                     float* __restrict__ dy, int64_t rows,
@@ -227,8 +229,9 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd(const float* __restrict__ g,
     __shared__ float sm[kBlock];
     int64_t r0, r1;
     block_rows(blk, rows, r0, r1);
-    for (int32_t cc = 0; cc < d; cc += kBlock) {
-        const int cwe = d - cc < kBlock ? d - cc : kBlock;     // columns in this chunk
+    {
+        const int32_t cc = (int32_t)blockIdx.y * kActColumns;
+        const int cwe = d - cc < kActColumns ? d - cc : kActColumns;   // columns of this block
         const int rpp = kBlock / cwe;                          // rows per pass
         const int rsub = threadIdx.x / cwe;
         const int32_t c = cc + threadIdx.x % cwe;
@@ -267,9 +270,8 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd(const float* __restrict__ g,
     }
 }
 
-// float4 variant for widths that are multiples of 4: cw = d / 4 threads cover one row, the
-// block walks its 256 rows 256 / cw at a time with four row groups in flight, and the row
-// groups are combined through LDS in a fixed order.
+// float4 variant for widths that are multiples of 4: sixteen threads cover a block's part of a row, the
+// block walks its 256 rows sixteen at a time with four such groups in flight.
 __global__ __launch_bounds__(kBlock) void k_act_bwd_vec(const float* __restrict__ g,
                                                         const float* __restrict__ act,
                                                         float* __restrict__ dy, int64_t rows,
@@ -281,8 +283,10 @@ __global__ __launch_bounds__(kBlock) void k_act_bwd_vec(const float* __restrict_
     const int cw = d / 4;
     int64_t r0, r1;
     block_rows(blk, rows, r0, r1);
-    for (int cc = 0; cc < cw; cc += kBlock) {
-        const int cwe = cw - cc < kBlock ? cw - cc : kBlock;   // float4 columns in this chunk
+    {
+        constexpr int kVectors = kActColumns / 4;
+        const int cc = (int)blockIdx.y * kVectors;
+        const int cwe = cw - cc < kVectors ? cw - cc : kVectors;   // float4 columns of this block
         const int rpp = kBlock / cwe;                          // rows per pass
         const int rsub = threadIdx.x / cwe, cidx = cc + threadIdx.x % cwe;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -735,14 +739,15 @@ void launch_act_bwd(const float* g, const float* act, float* dy, int64_t rows, i
     const int64_t blocks = rb ? rb->nblocks : (rows + kRowsPerBlockAct - 1) / kRowsPerBlockAct;
     const int2* blk = rb ? rb->rows : nullptr;
     if (!act && !gb) return;
+    const dim3 grid((unsigned)blocks, (unsigned)((d + kActColumns - 1) / kActColumns));
     const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(act) |
                                      reinterpret_cast<uintptr_t>(dy) |
                                      reinterpret_cast<uintptr_t>(partial)) & 15) == 0;
     if (vec)
-        hipLaunchKernelGGL(k_act_bwd_vec, dim3((unsigned)blocks), dim3(kBlock), 0, s, g, act, dy, rows,
+        hipLaunchKernelGGL(k_act_bwd_vec, grid, dim3(kBlock), 0, s, g, act, dy, rows,
                            d, partial, scale, row_on, blk);
     else
-        hipLaunchKernelGGL(k_act_bwd, dim3((unsigned)blocks), dim3(kBlock), 0, s, g, act, dy, rows, d,
+        hipLaunchKernelGGL(k_act_bwd, grid, dim3(kBlock), 0, s, g, act, dy, rows, d,
                            partial, scale, row_on, blk);
     if (gb) launch_colsum_finish(partial, blocks, d, gb, s, d, rb, partial + blocks * d);
 }

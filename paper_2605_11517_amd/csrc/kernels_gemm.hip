@@ -343,8 +343,31 @@ __global__ __launch_bounds__(kThreads, 3) void k_gemm(const GemmArgs g)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * g.ldc] = acc[i][j][r] + bv;
             } else if (inside) {
+                // (what is added is read before anything is stored, sixteen loads in flight: element by
+                // element the aggregate of a GraphSAGE layer cost 33 us on 40,000 rows of 256)
+                float v[16], o[16];
+                auto load16 = [&](const float* p, int64_t ld) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) put(row0 + 8 * (r >> 2) + (r & 3), col, acc[i][j][r] + bv);
+                    for (int r = 0; r < 16; ++r) o[r] = p[row0 * ld + col + (8 * (r >> 2) + (r & 3)) * ld];
+                };
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r] + bv;
+                if (g.add) {
+                    load16(g.add, g.ldadd);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] += o[r];
+                }
+                if (g.relu) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
+                }
+                if (g.accumulate) {
+                    load16(cbase, g.ldc);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] += o[r];
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * g.ldc] = v[r];
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
