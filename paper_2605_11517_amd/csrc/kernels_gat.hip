@@ -995,6 +995,78 @@ __global__ __launch_bounds__(kBlock) void k_gat_dots(GatDotArgs g)
     }
 }
 
+// The same for rows of 5 to 16 vectors (a head of eight in a layer of 256: 1.02 -> 0.69 ms on 6 M entries): a slot of G lanes takes an item
+// of its own, a segment or a whole short row, the short rows longest first.  Bound by rows in flight; a
+// wavefront that walks one row of twenty entries keeps a third of its lanes busy.  Eight entries at a
+// time: their partial products are summed across the lanes and transposed in one go (a sum in the order
+// of the loop above, entry u ending in lane u), 7 shuffles and one store instead of 24 and 8.
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_gat_dots_slots(GatDotArgs g)
+{
+    static_assert(G == 8 || G == 16, "eight entries, eight or sixteen lanes");
+    constexpr int S = kWave / G, U = 8;
+    const int lane = threadIdx.x % kWave, slot = lane / G, gl = lane % G;
+    unsigned blk = blockIdx.x;
+    if (g.nslice > 1) {
+        const int64_t hd = blk % (unsigned)g.nslice;
+        blk /= (unsigned)g.nslice;
+        g.a_rows += hd * g.d;
+        g.b_rows += hd * g.d;
+        g.dy += hd * g.d;
+        g.dal += hd * g.dal_stride;
+    }
+    const int64_t item = ((int64_t)blk * (kBlock / kWave) + threadIdx.x / kWave) * S + slot;
+    int64_t eb = 0;
+    int32_t len = 0, row = 0;
+    if (item < g.it.nsegs) {
+        eb = g.it.seg_begin[item];
+        len = g.it.seg_len[item];
+        row = g.it.seg_row[item];
+    } else if (item < g.it.nsegs + g.it.nshort) {
+        row = g.it.rows_sorted[item - g.it.nsegs] & 0x7FFFFFFF;
+        eb = g.rp[row];
+        len = (int32_t)(g.rp[row + 1] - eb);
+    }
+    int32_t maxlen = len;
+#pragma unroll
+    for (int m = G; m < kWave; m <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, m, kWave));
+    // lanes past the row's end multiply by zero what they read from column 0
+    const bool live = gl * 4 < g.d;
+    const int cv = live ? gl * 4 : 0;
+    const float4 y = live ? *reinterpret_cast<const float4*>(g.dy + (int64_t)row * g.ld + cv) : make_float4(0.f, 0.f, 0.f, 0.f);
+    // a slot that has ended repeats its last entry (no entry at all: row 0), without storing
+    auto column = [&](int32_t e) { return len > 0 ? g.col[eb + (e < len ? e : len - 1)] : 0; };
+    int32_t next = column(gl % U);
+    for (int32_t e0 = 0; e0 < maxlen; e0 += U) {
+        const int32_t mine = next;
+        float4 h[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t c = __shfl(mine, slot * G + u, kWave);
+            const float* src = c < g.n_own ? g.a_rows + (int64_t)c * g.ld : g.b_rows + ((int64_t)c - g.n_own) * g.ld;
+            h[u] = *reinterpret_cast<const float4*>(src + cv);
+        }
+        next = column(e0 + U + gl % U);
+        float a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float acc = 0.f;
+            acc += (h[u].x * y.x + h[u].y * y.y) + (h[u].z * y.z + h[u].w * y.w);
+            a[u] = acc;
+        }
+#pragma unroll
+        for (int m = 1, n = U / 2; m < U; m <<= 1, n >>= 1)
+#pragma unroll
+            for (int j = 0; j < n; ++j) {
+                const bool odd = (gl & m) != 0;
+                const float keep = odd ? a[2 * j + 1] : a[2 * j], send = odd ? a[2 * j] : a[2 * j + 1];
+                a[j] = keep + __shfl_xor(send, m, kWave);
+            }
+        if (G == 16) a[0] += __shfl_xor(a[0], 8, kWave);
+        if (gl < U && e0 + gl < len) g.dal[eb + e0 + gl - g.e0] = a[0];
+    }
+}
+
 // gH[r, j] += gs_src[r nh] a_src[j] + gs_dst[r nh] a_dst[j] for the rows of one partition (one
 // head: its scores are nh floats apart), and the per-block partial column sums
 // sum_r gs_src[r] H[r, j] (first f columns of `partial` rows) and sum_r gs_dst[r] H[r, j] (next f
@@ -1220,9 +1292,10 @@ void launch_gat_dots(const int64_t* rp, const int32_t* col, int64_t e0, int64_t 
     g.nslice = nslice; g.dal_stride = dal_stride;
     const dim3 grid((unsigned)((nitems + 3) / 4 * nslice)), block(kBlock);
     const int vecs = d / 4;
+    auto slots = [&](int per_wave) { return dim3((unsigned)((items.nsegs + items.nshort + 4 * per_wave - 1) / (4 * per_wave) * nslice)); };
     if (vecs <= 4) hipLaunchKernelGGL((k_gat_dots<4, 1>), grid, block, 0, s, g);
-    else if (vecs <= 8) hipLaunchKernelGGL((k_gat_dots<8, 1>), grid, block, 0, s, g);
-    else if (vecs <= 16) hipLaunchKernelGGL((k_gat_dots<16, 1>), grid, block, 0, s, g);
+    else if (vecs <= 8) hipLaunchKernelGGL((k_gat_dots_slots<8>), slots(8), block, 0, s, g);
+    else if (vecs <= 16) hipLaunchKernelGGL((k_gat_dots_slots<16>), slots(4), block, 0, s, g);
     else if (vecs <= 32) hipLaunchKernelGGL((k_gat_dots<32, 1>), grid, block, 0, s, g);
     // 1 KB rows: four 16-lane slots with four vectors per lane keep 16 source rows in flight per
     // wavefront and need four shuffle steps per entry (one 64-lane slot: 4 rows, six steps)
