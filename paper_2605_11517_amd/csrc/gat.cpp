@@ -138,7 +138,7 @@ void gat_transform_fwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
         GemmSeg seg;
         seg.a = in_own; seg.lda = v.din;
         seg.b = v.W; seg.ldb = v.dout; seg.k = v.din;
-        launch_gemm_nn(&seg, 1, Hp, v.ldh, v.np, v.side ? v.dout : v.f, GemmEpilogue{}, s);
+        launch_gemm_f32_nn(&seg, 1, Hp, v.ldh, v.np, v.side ? v.dout : v.f, GemmEpilogue{}, s);
     }
     Timed t(c, s, GNN_K_OTHER);
     launch_gat_scores(v0.H + v0.own(), v0.ldh, v0.f, v0.np, v0.a_src, v0.a_dst, v0.ssrc + v0.r0 * nh,
@@ -393,7 +393,7 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
         }
         if (gprev) {
             Timed t(c, s, GNN_K_GEMM_DZ);   // the only term of grad A^{l-1}_p: written, not accumulated
-            launch_gemm_nt(gHp, v0.ldh, v0.W, v0.dout, gprev, v0.din, v0.np, v0.din, v0.dout, GemmEpilogue{}, s);
+            launch_gemm_f32_nt(gHp, v0.ldh, v0.W, v0.dout, gprev, v0.din, v0.np, v0.din, v0.dout, GemmEpilogue{}, s);
         }
         return;
     }
@@ -425,7 +425,7 @@ void gat_transform_bwd(gnn_ctx* c, int32_t layer, int32_t p, hipStream_t s)
             }
             GemmEpilogue ep;
             ep.accumulate = h0 > 0 ? 1 : 0;
-            launch_gemm_nt2(segs, nseg, gprev, v0.din, v0.np, v0.din, ep, s);
+            launch_gemm_f32_nt2(segs, nseg, gprev, v0.din, v0.np, v0.din, ep, s);
         }
     }
 }

@@ -517,7 +517,7 @@ void weight_grad(gnn_ctx* c, const void* a, int64_t lda, const void* b, int64_t 
                             sp ? &sp->narrow : nullptr);
     else
         launch_gemm_tn((const float*)a, lda, (const float*)b, ldb, out, ldc, m, n, rows, chunk, partial, s,
-                       sp ? &sp->narrow : nullptr);
+                       sp ? &sp->narrow : nullptr, c->model == GNN_GAT);
 }
 
 void compute_fwd(gnn_ctx* c, int32_t layer, int32_t p, const char* in_own, char* out_own, hipStream_t s)

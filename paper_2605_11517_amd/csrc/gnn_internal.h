@@ -310,7 +310,19 @@ struct TnParts {
 // `partial` then holds nchunks + nslots matrices.
 void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
                     int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t chunk, float* partial,
-                    hipStream_t s, const TnParts* parts = nullptr);
+                    hipStream_t s, const TnParts* parts = nullptr, bool f32_instruction = false);
+// The same products on the fp32 matrix instruction, for attention layers (no GemmEpilogue::add); tn
+// leaves its partial products in `partial` and does not sum them.
+void launch_gemm_f32_nn(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64_t m, int32_t n,
+                        const GemmEpilogue& ep, hipStream_t s);
+void launch_gemm_f32_nt(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
+                        int64_t ldc, int64_t m, int32_t n, int32_t k, const GemmEpilogue& ep,
+                        hipStream_t s);
+void launch_gemm_f32_nt2(const GemmSeg* segs, int nseg, float* c, int64_t ldc, int64_t m, int32_t n,
+                         const GemmEpilogue& ep, hipStream_t s);
+void launch_gemm_f32_tn(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
+                        int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t chunk, float* partial,
+                        hipStream_t s, const TnParts* parts);
 // sums[slot of group] = sum of the group's splits; c += sums[0], then sums[1], ...
 void launch_reduce_groups(const float* partial, int64_t stride, int32_t m, int32_t n, const TnParts& parts,
                           float* sums, hipStream_t s);

@@ -608,7 +608,7 @@ int64_t gemm_tn_chunk(int64_t rows, int32_t m, int32_t n)
 
 void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, float* c,
                     int64_t ldc, int32_t m, int32_t n, int64_t kdim, int64_t chunk, float* partial,
-                    hipStream_t s, const TnParts* parts)
+                    hipStream_t s, const TnParts* parts, bool f32_instruction)
 {
     if (kdim <= 0 || m <= 0 || n <= 0) return;
     const int splits = parts ? parts->nchunks : (int)((kdim + chunk - 1) / chunk);
@@ -620,7 +620,8 @@ void launch_gemm_tn(const float* a, int64_t lda, const float* b, int64_t ldb, fl
     g.split_chunk = chunk;
     g.split_stride = (int64_t)m * n;
     g.splits = parts ? parts->chunks : nullptr;
-    launch_gemm<false, false>(g, splits, s);
+    if (f32_instruction) launch_gemm_f32_tn(a, lda, b, ldb, c, ldc, m, n, kdim, chunk, partial, s, parts);
+    else launch_gemm<false, false>(g, splits, s);
     if (parts) {
         float* sums = partial + (int64_t)splits * m * n;
         launch_reduce_groups(partial, (int64_t)m * n, m, n, *parts, sums, s);
