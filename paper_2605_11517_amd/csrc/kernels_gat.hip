@@ -995,7 +995,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dots(GatDotArgs g)
     }
 }
 
-// The same for rows of 5 to 16 vectors (a head of eight in a layer of 256: 1.02 -> 0.69 ms on 6 M entries): a slot of G lanes takes an item
+// The same for rows of 5 to 16 vectors (a head of eight in a layer of 256: 1.02 -> 0.74 ms on 6 M entries): a slot of G lanes takes an item
 // of its own, a segment or a whole short row, the short rows longest first.  Bound by rows in flight; a
 // wavefront that walks one row of twenty entries keeps a third of its lanes busy.  Eight entries at a
 // time: their partial products are summed across the lanes and transposed in one go (a sum in the order
